@@ -128,15 +128,20 @@ def _ptr(t: Optional[torch.Tensor], dtype: Optional[torch.dtype] = None) -> int:
     ``dtype`` is given, the element type the entry point reads the buffer as."""
     if t is None:
         return 0
-    if not t.is_cuda or not t.is_contiguous():
+    if not (t.is_cuda and t.is_contiguous()):
         raise ValueError("tensors handed to the library must be contiguous device tensors")
-    if dtype is not None and t.dtype != dtype:
+    if dtype is not None and t.dtype is not dtype:
         raise TypeError(f"expected a {dtype} tensor, got {t.dtype}")
     return t.data_ptr()
 
 
+_raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    """The current stream's handle.  torch.cuda.current_stream() builds a Stream object first: 2.9 us of a call that takes 9,
+    against 0.2 us for the handle alone."""
+    return _raw_stream(_current_device())
 
 
 def _ws(nbytes: int, ws: Optional[torch.Tensor], device) -> Tuple[Optional[torch.Tensor], int]:
