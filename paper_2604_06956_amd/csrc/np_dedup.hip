@@ -124,11 +124,11 @@ struct SortPairPolicy {
 // ---- after the sort: segment heads -> ranks ------------------------------------------------------------
 
 #ifndef NP_HEAD_THREADS
-#define NP_HEAD_THREADS 256
+#define NP_HEAD_THREADS 512
 #endif
 constexpr int kHeadThreads = NP_HEAD_THREADS;
 #ifndef NP_HEAD_IPT
-#define NP_HEAD_IPT 8
+#define NP_HEAD_IPT 4
 #endif
 constexpr int kHeadIPT = NP_HEAD_IPT;
 constexpr int kHeadTile = kHeadThreads * kHeadIPT;
@@ -143,123 +143,171 @@ __host__ __device__ __forceinline__ int64_t head_chunk_begin(int num_tiles, int 
     return (static_cast<int64_t>(c) * num_tiles / num_chunks) * kHeadTile;
 }
 
-// Number of segment heads (sorted[i] != sorted[i-1], position 0 is a head) in every chunk of the emit kernel.  A pure
-// streaming read, so it runs with four times the emit kernel's threads per block (0.058 -> 0.041 ms).
-constexpr int kCountThreads = 1024;
-template <typename K>
-__global__ void __launch_bounds__(kCountThreads)
-dedup_count_heads_kernel(const K* __restrict__ sorted, int n, int num_tiles, int num_chunks, int* __restrict__ chunk_heads) {
-    __shared__ int wsum[kCountThreads / kWave];
-    const int64_t lo = head_chunk_begin(num_tiles, num_chunks, blockIdx.x);
-    int64_t hi = head_chunk_begin(num_tiles, num_chunks, blockIdx.x + 1);
-    if (hi > n) hi = n;
-    int cnt = 0;
-    for (int64_t base = lo; base < hi; base += static_cast<int64_t>(kCountThreads) * 8) {
+// Number of segment heads (sorted[i] != sorted[i-1], position 0 is a head) among positions [lo, hi) and the last of them (-1:
+// none), over a block of THREADS threads; every thread gets both.  `red` holds 2 * THREADS / 64 ints.
+template <int THREADS, typename K>
+__device__ __forceinline__ void count_heads_range(const K* __restrict__ sorted, int64_t lo, int64_t hi, int* red, int* heads, int* last_head) {
+    int cnt = 0, last = -1;
+    for (int64_t base = lo; base < hi; base += static_cast<int64_t>(THREADS) * 8) {
         K cur[8], prv[8];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {  // sixteen independent loads in flight per thread
-            const int64_t i = base + q * kCountThreads + threadIdx.x;
-            cur[q] = K(0);
-            prv[q] = K(0);
-            if (i < hi) {
-                cur[q] = sorted[i];
-                if (i > 0) prv[q] = sorted[i - 1];
-            }
+        for (int q = 0; q < 8; ++q) {  // sixteen independent loads in flight per thread, past the end from the last position
+            const int64_t i = base + q * THREADS + threadIdx.x;
+            const int64_t ic = i < hi ? i : hi - 1;
+            cur[q] = sorted[ic];
+            prv[q] = sorted[ic > 0 ? ic - 1 : 0];
         }
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-            const int64_t i = base + q * kCountThreads + threadIdx.x;
-            if (i < hi) cnt += (i == 0 || cur[q] != prv[q]) ? 1 : 0;
+            const int64_t i = base + q * THREADS + threadIdx.x;
+            if (i < hi && (i == 0 || cur[q] != prv[q])) {
+                ++cnt;
+                last = static_cast<int>(i);
+            }
         }
-    }
-#pragma unroll
-    for (int d = kWave / 2; d > 0; d >>= 1) cnt += __shfl_xor(cnt, d, kWave);
-    if (__lane_id() == 0) wsum[threadIdx.x / kWave] = cnt;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int s = 0;
-        for (int i = 0; i < kCountThreads / kWave; ++i) s += wsum[i];
-        chunk_heads[blockIdx.x] = s;
-    }
-}
-
-// One block per chunk: ranks every position, writes unique / occ_offsets at heads and scatters inverse.
-template <typename K>
-__global__ void __launch_bounds__(kHeadThreads)
-dedup_emit_kernel(const K* __restrict__ sorted, const int32_t* __restrict__ occ, int n, int num_tiles, int num_chunks,
-                  const int* __restrict__ chunk_heads, int64_t* __restrict__ unique, int32_t* __restrict__ inverse,
-                  int32_t* __restrict__ occ_offsets, int32_t* __restrict__ d_num_unique) {
-    __shared__ int scan_tmp[16];
-    __shared__ int red[kHeadThreads / kWave];
-    const int c = blockIdx.x;
-    // heads in all earlier chunks (num_chunks <= kEmitChunks, a handful of loads per thread)
-    int before = 0, all = 0;
-    for (int i = threadIdx.x; i < num_chunks; i += kHeadThreads) {
-        const int h = chunk_heads[i];
-        all += h;
-        if (i < c) before += h;
     }
 #pragma unroll
     for (int d = kWave / 2; d > 0; d >>= 1) {
-        before += __shfl_xor(before, d, kWave);
-        all += __shfl_xor(all, d, kWave);
+        cnt += __shfl_xor(cnt, d, kWave);
+        const int o = __shfl_xor(last, d, kWave);
+        last = o > last ? o : last;
     }
-    if (__lane_id() == 0) red[threadIdx.x / kWave] = before;
-    __syncthreads();
-    before = 0;
-    for (int i = 0; i < kHeadThreads / kWave; ++i) before += red[i];
-    __syncthreads();
-    if (c == 0) {
-        if (__lane_id() == 0) red[threadIdx.x / kWave] = all;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            int U = 0;
-            for (int i = 0; i < kHeadThreads / kWave; ++i) U += red[i];
-            *d_num_unique = U;
-            occ_offsets[U] = n;
-        }
+    if (__lane_id() == 0) {
+        red[threadIdx.x / kWave] = cnt;
+        red[THREADS / kWave + threadIdx.x / kWave] = last;
     }
+    __syncthreads();
+    cnt = 0;
+#pragma unroll
+    for (int i = 0; i < THREADS / kWave; ++i) {
+        cnt += red[i];
+        const int o = red[THREADS / kWave + i];
+        last = o > last ? o : last;
+    }
+    *heads = cnt;
+    *last_head = last;
+}
+
+// Heads of every chunk of the emit kernel.  A pure streaming read, so it runs with twice the emit kernel's threads per block.
+constexpr int kCountThreads = 1024;
+template <typename K>
+__global__ void __launch_bounds__(kCountThreads)
+dedup_count_heads_kernel(const K* __restrict__ sorted, int n, int num_tiles, int num_chunks, int2* __restrict__ chunk_heads) {
+    __shared__ int red[2 * kCountThreads / kWave];
+    const int64_t lo = head_chunk_begin(num_tiles, num_chunks, blockIdx.x);
+    int64_t hi = head_chunk_begin(num_tiles, num_chunks, blockIdx.x + 1);
+    if (hi > n) hi = n;
+    int heads, last;
+    count_heads_range<kCountThreads>(sorted, lo, hi, red, &heads, &last);
+    if (threadIdx.x == 0) chunk_heads[blockIdx.x] = make_int2(heads, last);
+}
+
+// One block per chunk: ranks every position, writes unique / occ_offsets / counts at heads and scatters inverse.  A wave holds
+// 64 consecutive positions per round, so ranks are bit counts of one ballot, and the head before a head is the next lower
+// bit: its distance is the multiplicity of the key before.  SELF (few positions): a chunk is one tile and the block counts the
+// heads before it itself, which saves dedup_count_heads's launch.
+template <typename K, bool SELF>
+__global__ void __launch_bounds__(kHeadThreads)
+dedup_emit_kernel(const K* __restrict__ sorted, const int32_t* __restrict__ occ, int n, int num_tiles, int num_chunks,
+                  const int2* __restrict__ chunk_heads, int64_t* __restrict__ unique, int32_t* __restrict__ inverse,
+                  int32_t* __restrict__ counts, int32_t* __restrict__ occ_offsets, int32_t* __restrict__ d_num_unique) {
+    constexpr int NW = kHeadThreads / kWave;
+    __shared__ int red[2 * NW];
+    __shared__ int wave_count[2][NW], wave_last[2][NW];  // double-buffered: one barrier per tile
+    const int c = blockIdx.x, lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
     const int64_t lo = head_chunk_begin(num_tiles, num_chunks, c);
     int64_t hi = head_chunk_begin(num_tiles, num_chunks, c + 1);
     if (hi > n) hi = n;
-    int running = before;  // heads before the current tile
-    for (int64_t tile = lo; tile < hi; tile += kHeadTile) {
-        // blocked arrangement: thread t owns positions tile + t*IPT .. +IPT-1, so a thread-level scan is in order
-        const int64_t p0 = tile + static_cast<int64_t>(threadIdx.x) * kHeadIPT;
-        K k[kHeadIPT];
-        int flag[kHeadIPT];
-        K prev = K(0);
-        if (p0 > 0 && p0 < hi) prev = sorted[p0 - 1];
-        int local = 0;
-#pragma unroll
-        for (int i = 0; i < kHeadIPT; ++i) {
-            const int64_t p = p0 + i;
-            flag[i] = 0;
-            if (p < hi) {
-                k[i] = sorted[p];
-                flag[i] = (p == 0 || k[i] != prev) ? 1 : 0;
-                prev = k[i];
-            }
-            local += flag[i];
+    int running = 0, last = -1;  // heads before the current tile, and the last of them
+    if (SELF) {
+        count_heads_range<kHeadThreads>(sorted, 0, lo, red, &running, &last);
+    } else {
+        for (int i = threadIdx.x; i < c; i += kHeadThreads) {  // num_chunks <= kEmitChunks, a handful of loads per thread
+            const int2 h = chunk_heads[i];
+            running += h.x;
+            last = h.y > last ? h.y : last;
         }
-        int total;
-        int ex = block_excl_scan<kHeadThreads / kWave>(local, scan_tmp, &total);
-        int rank = running + ex;  // heads strictly before p0
+#pragma unroll
+        for (int d = kWave / 2; d > 0; d >>= 1) {
+            running += __shfl_xor(running, d, kWave);
+            const int o = __shfl_xor(last, d, kWave);
+            last = o > last ? o : last;
+        }
+        if (lane == 0) {
+            red[w] = running;
+            red[NW + w] = last;
+        }
+        __syncthreads();
+        running = 0;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+            running += red[i];
+            last = red[NW + i] > last ? red[NW + i] : last;
+        }
+    }
+    const uint64_t lt = lanemask_lt();
+    int buf = 0;
+    for (int64_t tile = lo; tile < hi; tile += kHeadTile, buf ^= 1) {
+        const int64_t wbase = tile + static_cast<int64_t>(w) * (kHeadIPT * kWave);
+        K k[kHeadIPT], prv[kHeadIPT];
+        int j[kHeadIPT];
 #pragma unroll
         for (int i = 0; i < kHeadIPT; ++i) {
-            const int64_t p = p0 + i;
+            const int64_t p = wbase + i * kWave + lane;
+            const int64_t pc = p < hi ? p : hi - 1;
+            k[i] = sorted[pc];
+            prv[i] = sorted[pc > 0 ? pc - 1 : 0];
+            j[i] = occ[pc];
+        }
+        uint64_t heads[kHeadIPT];
+        int wc = 0, wl = -1;
+#pragma unroll
+        for (int i = 0; i < kHeadIPT; ++i) {
+            const int64_t p = wbase + i * kWave + lane;
+            heads[i] = __ballot(p < hi && (p == 0 || k[i] != prv[i]));
+            wc += __popcll(heads[i]);
+            if (heads[i]) wl = static_cast<int>(wbase) + i * kWave + 63 - __clzll(static_cast<long long>(heads[i]));
+        }
+        if (lane == 0) {
+            wave_count[buf][w] = wc;
+            wave_last[buf][w] = wl;
+        }
+        lds_barrier();
+        int rank = running, prev_head = last;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+            const int wci = wave_count[buf][i], wli = wave_last[buf][i];
+            if (i < w) {
+                rank += wci;
+                prev_head = wli > prev_head ? wli : prev_head;
+            }
+            running += wci;
+            last = wli > last ? wli : last;
+        }
+#pragma unroll
+        for (int i = 0; i < kHeadIPT; ++i) {
+            const int64_t p = wbase + i * kWave + lane;
+            const bool head = (heads[i] >> lane) & 1ull;
+            const uint64_t below = heads[i] & lt;
+            const int u = rank + __popcll(below) - (head ? 0 : 1);
             if (p < hi) {
-                rank += flag[i];
-                const int u = rank - 1;
-                if (flag[i]) {
+                if (head) {
                     unique[u] = static_cast<int64_t>(k[i]);
                     occ_offsets[u] = static_cast<int32_t>(p);
+                    const int before = below ? static_cast<int>(wbase) + i * kWave + 63 - __clzll(static_cast<long long>(below)) : prev_head;
+                    if (u > 0) counts[u - 1] = static_cast<int>(p) - before;
                 }
                 // a plain store: L2 merges the partial lines (a non-temporal one doubles the kernel's time)
-                if (inverse) inverse[occ[p]] = u;
+                if (inverse) inverse[j[i]] = u;
             }
+            rank += __popcll(heads[i]);
+            if (heads[i]) prev_head = static_cast<int>(wbase) + i * kWave + 63 - __clzll(static_cast<long long>(heads[i]));
         }
-        running += total;
+    }
+    if (hi == n && lo < hi && threadIdx.x == 0) {  // the block of the last position
+        *d_num_unique = running;
+        occ_offsets[running] = n;
+        counts[running - 1] = n - last;
     }
 }
 
@@ -280,18 +328,19 @@ dedup_emit_kernel(const K* __restrict__ sorted, const int32_t* __restrict__ occ,
 // and writes the ranks it finds with coalesced stores, and the scatter skips the positions that pass covers.  The scatter
 // 0.54 -> 0.38 ms, but the pass takes 0.30 ms (every probe moves a 128-byte line from L2 to L1, 5.4 GB in all): np_dedup 1.90 ms
 // against 1.79.  A random 4-byte read costs this memory system as much as a random 4-byte write.
+constexpr int kOrdThreads = 256;
 constexpr int kOrdIPT = 4;
-constexpr int kOrdTile = kHeadThreads * kOrdIPT;  // 1024 sorted positions
+constexpr int kOrdTile = kOrdThreads * kOrdIPT;  // 1024 sorted positions
 constexpr int kOrdBuckets = 1024;
 // Below tune_get(kTuneEmitOrderMinN) lookups (4 M unless changed) the five extra launches cost more than the merged stores return.
 
 // Heads per tile and the tile's bucket; one wave per tile (sixteen positions per lane), four tiles per block, no LDS.
 template <typename K>
-__global__ void __launch_bounds__(kHeadThreads)
+__global__ void __launch_bounds__(kOrdThreads)
 dedup_tile_heads_kernel(const K* __restrict__ sorted, const int32_t* __restrict__ occ, int n, int num_tiles,
                         int32_t* __restrict__ tile_heads, uint32_t* __restrict__ tile_bucket) {
     constexpr int PER_LANE = kOrdTile / kWave;
-    const int tile = blockIdx.x * (kHeadThreads / kWave) + threadIdx.x / kWave;
+    const int tile = blockIdx.x * (kOrdThreads / kWave) + threadIdx.x / kWave;
     if (tile >= num_tiles) return;  // whole waves leave together
     const int lane = __lane_id();
     const int64_t first = static_cast<int64_t>(tile) * kOrdTile;
@@ -372,7 +421,7 @@ struct EmitOrderPolicy {
 // One block per tile, in the given order: die x (blocks x, x + 8, ...) first runs its contiguous share of the ordered
 // tiles, i.e. one eighth of the bands of the batch, then every eighth of the others.
 template <typename K>
-__global__ void __launch_bounds__(kHeadThreads)
+__global__ void __launch_bounds__(kOrdThreads)
 dedup_emit_tiles_kernel(const K* __restrict__ sorted, const int32_t* __restrict__ occ, int n, int num_tiles,
                         const int32_t* __restrict__ tile_base, const int32_t* __restrict__ order,
                         const int32_t* __restrict__ order_offsets, int64_t* __restrict__ unique, int32_t* __restrict__ inverse,
@@ -426,7 +475,7 @@ dedup_emit_tiles_kernel(const K* __restrict__ sorted, const int32_t* __restrict_
         local += flag[i];
     }
     int total;
-    int rank = tile_base[tile] + block_excl_scan<kHeadThreads / kWave>(local, scan_tmp, &total);  // heads strictly before p0
+    int rank = tile_base[tile] + block_excl_scan<kOrdThreads / kWave>(local, scan_tmp, &total);  // heads strictly before p0
 #pragma unroll
     for (int i = 0; i < kOrdIPT; ++i) {
         const int64_t p = p0 + i;
@@ -474,7 +523,7 @@ inline DedupWs dedup_ws_layout(int32_t n, int32_t key_bits) {
     w.total = 2 * w.key_bytes + (key_bits <= 32 ? 0 : align_up(4 * static_cast<size_t>(n), 256))
               + align_up(4 * part_hist_elems(w.plan, w.max_bins), 256)        // histogram matrix
               + align_up(4 * static_cast<size_t>(w.max_bins), 256)            // bin totals
-              + align_up(4 * static_cast<size_t>(kEmitChunks), 256);          // heads per chunk
+              + align_up(8 * static_cast<size_t>(kEmitChunks), 256);          // heads per chunk, and the last of them
     // the tile-ordered emit: heads, bases and order of the tiles, bucket offsets, its own partition scratch
     const size_t ord_tiles = (static_cast<size_t>(n) + kOrdTile - 1) / kOrdTile;
     w.total += 4 * align_up(4 * ord_tiles, 256) + align_up(4 * static_cast<size_t>(kOrdBuckets + 2), 256)
@@ -492,7 +541,7 @@ int dedup_impl(const int64_t* keys, int32_t n, int32_t key_bits, int64_t* unique
     uint32_t* vtmp = sizeof(K) == 4 ? nullptr : cur.take<uint32_t>(n);
     uint32_t* H = cur.take<uint32_t>(part_hist_elems(L.plan, L.max_bins));
     uint32_t* bin_total = cur.take<uint32_t>(L.max_bins);
-    int* chunk_heads = cur.take<int>(kEmitChunks);
+    int2* chunk_heads = cur.take<int2>(kEmitChunks);
     uint32_t* vocc = reinterpret_cast<uint32_t*>(occ);
 
     const int P = L.passes.passes;
@@ -550,29 +599,34 @@ int dedup_impl(const int64_t* keys, int32_t n, int32_t key_bits, int64_t* unique
         const ChunkPlan oplan = make_chunk_plan(ord_tiles);
         uint32_t* oH = cur.take<uint32_t>(part_hist_elems(oplan, kOrdBuckets + 1));
         uint32_t* obin = cur.take<uint32_t>(kOrdBuckets + 1);
-        constexpr int kTilesPerBlock = kHeadThreads / kWave;
+        constexpr int kTilesPerBlock = kOrdThreads / kWave;
         NP_LAUNCH("dedup_tile_heads", dedup_tile_heads_kernel<K>, dim3((ord_tiles + kTilesPerBlock - 1) / kTilesPerBlock),
-                  dim3(kHeadThreads), 0, stream, sorted, occ, n, ord_tiles, tile_heads, tile_bucket);
+                  dim3(kOrdThreads), 0, stream, sorted, occ, n, ord_tiles, tile_heads, tile_bucket);
         NP_LAUNCH("dedup_tile_scan", dedup_tile_scan_kernel, dim3(1), dim3(1024), 0, stream, tile_heads, ord_tiles, n, tile_base,
                   occ_offsets, d_num_unique);
         EmitOrderPolicy pol{tile_bucket, order};
         run_partition_pass(pol, ord_tiles, nullptr, kOrdBuckets + 1, 11, oplan, oH, obin, nullptr, order_offsets, stream,
                            "dedup_order_hist", "dedup_order_colscan", "dedup_order_scatter");
         const unsigned grid = static_cast<unsigned>((ord_tiles + 2 * kNumXcd + kNumXcd - 1) / kNumXcd * kNumXcd);
-        NP_LAUNCH("dedup_emit", dedup_emit_tiles_kernel<K>, dim3(grid), dim3(kHeadThreads), 0, stream, sorted, occ, n, ord_tiles,
+        NP_LAUNCH("dedup_emit", dedup_emit_tiles_kernel<K>, dim3(grid), dim3(kOrdThreads), 0, stream, sorted, occ, n, ord_tiles,
                   tile_base, order, order_offsets, unique, inverse, occ_offsets);
+        int cgrid = (n + 255) / 256;
+        if (cgrid > 4096) cgrid = 4096;
+        NP_LAUNCH("dedup_counts", dedup_counts_kernel, dim3(cgrid), dim3(256), 0, stream, occ_offsets, d_num_unique, n, counts);
     } else {
         // chunks of whole head-tiles, at most kEmitChunks of them
         const int num_tiles = static_cast<int>((static_cast<int64_t>(n) + kHeadTile - 1) / kHeadTile);
         const int num_chunks = num_tiles < kEmitChunks ? num_tiles : kEmitChunks;
-        NP_LAUNCH("dedup_count_heads", dedup_count_heads_kernel<K>, dim3(num_chunks), dim3(kCountThreads), 0, stream, sorted, n,
-                  num_tiles, num_chunks, chunk_heads);
-        NP_LAUNCH("dedup_emit", dedup_emit_kernel<K>, dim3(num_chunks), dim3(kHeadThreads), 0, stream, sorted, occ, n,
-                  num_tiles, num_chunks, chunk_heads, unique, inverse, occ_offsets, d_num_unique);
+        if (n <= kSoloItems) {
+            NP_LAUNCH("dedup_emit", (dedup_emit_kernel<K, true>), dim3(num_chunks), dim3(kHeadThreads), 0, stream, sorted, occ, n, num_tiles,
+                      num_chunks, chunk_heads, unique, inverse, counts, occ_offsets, d_num_unique);
+        } else {
+            NP_LAUNCH("dedup_count_heads", dedup_count_heads_kernel<K>, dim3(num_chunks), dim3(kCountThreads), 0, stream, sorted, n,
+                      num_tiles, num_chunks, chunk_heads);
+            NP_LAUNCH("dedup_emit", (dedup_emit_kernel<K, false>), dim3(num_chunks), dim3(kHeadThreads), 0, stream, sorted, occ, n, num_tiles,
+                      num_chunks, chunk_heads, unique, inverse, counts, occ_offsets, d_num_unique);
+        }
     }
-    int cgrid = (n + 255) / 256;
-    if (cgrid > 4096) cgrid = 4096;
-    NP_LAUNCH("dedup_counts", dedup_counts_kernel, dim3(cgrid), dim3(256), 0, stream, occ_offsets, d_num_unique, n, counts);
     return launch_status();
 }
 

@@ -32,9 +32,9 @@ constexpr int kPartWaves = kPartThreads / kWave;
 constexpr int kPartIPT = NP_PART_IPT;
 constexpr int kPartTile = kPartThreads * kPartIPT;
 static_assert(kPartIPT * kWave <= 65535, "per-wave digit counters are 16 bits wide");
-// The 16-bit per-wave counters of one bin lie side by side and are scanned through one wide LDS access per kCntRowWaves waves.
-constexpr int kCntRowWaves = kPartWaves % 8 == 0 ? 8 : 4;
-static_assert(kPartWaves % kCntRowWaves == 0, "the per-wave 16-bit counters of one bin fill whole 8- or 16-byte words");
+// The 16-bit per-wave counters of one bin lie side by side and are scanned through one 16-byte LDS access per kCntRowWaves waves.
+constexpr int kCntRowWaves = 8;
+static_assert(kPartWaves % kCntRowWaves == 0, "the per-wave 16-bit counters of one bin fill whole 16-byte words");
 struct __align__(kCntRowWaves * 2) CntRow {
     uint32_t w[kCntRowWaves / 2];
 };
@@ -130,22 +130,21 @@ inline size_t part_scatter_lds_bytes(int bins, bool stage_digit) {
 
 // The counters of bin d lie side by side, wave w at column w ^ (cnt_swizzle(d) << 1): without the swizzle the lanes of one
 // wave, which differ in d only, would all fall into a quarter of the LDS banks.
-constexpr int kCntSwzShift = kPartWaves >= 16 ? 2 : (kPartWaves == 8 ? 3 : 4);
 constexpr int kCntSwzMask = kCntRowWaves / 2 - 1;
-__device__ __forceinline__ uint32_t cnt_swizzle(uint32_t d) { return (d >> kCntSwzShift) & kCntSwzMask; }
-__device__ __forceinline__ uint32_t cnt_index(uint32_t d, int w) { return d * kPartWaves + (static_cast<uint32_t>(w) ^ (cnt_swizzle(d) << 1)); }
+template <int WAVES>
+__device__ __forceinline__ uint32_t cnt_swizzle(uint32_t d) { return (d >> (WAVES >= 16 ? 2 : 3)) & kCntSwzMask; }
+template <int WAVES>
+__device__ __forceinline__ uint32_t cnt_index(uint32_t d, int w) {
+    return d * WAVES + (static_cast<uint32_t>(w) ^ (cnt_swizzle<WAVES>(d) << 1));
+}
 __device__ __forceinline__ void cnt_row_permute(CntRow& x, uint32_t swz) {  // its own inverse
-    if (kCntRowWaves == 8) {
-        if (swz & 1u) {
-            uint32_t t = x.w[0]; x.w[0] = x.w[1]; x.w[1] = t;
-            t = x.w[2 % (kCntRowWaves / 2)]; x.w[2 % (kCntRowWaves / 2)] = x.w[3 % (kCntRowWaves / 2)]; x.w[3 % (kCntRowWaves / 2)] = t;
-        }
-        if (swz & 2u) {
-            uint32_t t = x.w[0]; x.w[0] = x.w[2 % (kCntRowWaves / 2)]; x.w[2 % (kCntRowWaves / 2)] = t;
-            t = x.w[1]; x.w[1] = x.w[3 % (kCntRowWaves / 2)]; x.w[3 % (kCntRowWaves / 2)] = t;
-        }
-    } else if (swz & 1u) {
-        const uint32_t t = x.w[0]; x.w[0] = x.w[1]; x.w[1] = t;
+    if (swz & 1u) {
+        uint32_t t = x.w[0]; x.w[0] = x.w[1]; x.w[1] = t;
+        t = x.w[2]; x.w[2] = x.w[3]; x.w[3] = t;
+    }
+    if (swz & 2u) {
+        uint32_t t = x.w[0]; x.w[0] = x.w[2]; x.w[2] = t;
+        t = x.w[1]; x.w[1] = x.w[3]; x.w[3] = t;
     }
 }
 
@@ -174,23 +173,13 @@ __device__ __forceinline__ int64_t part_count(int n_host, const int* __restrict_
 //   __device__ void store(uint32_t dst, KeyT k, uint32_t v) const; item placed at output slot dst
 //   __device__ void placed(int64_t i, uint32_t dst) const;         input item i went to dst (may be a no-op)
 
-// A streaming read with one LDS add per run: it runs with kHistThreads threads per block, twice the scatter
-// kernel's, to keep enough loads in flight with two blocks per CU (0.21 -> 0.19 ms for three passes).
-template <class P>
-__global__ void __launch_bounds__(kHistThreads)
-part_hist_kernel(P pol, int n_host, const int* __restrict__ d_n, int bins, ChunkPlan plan, uint32_t* __restrict__ H) {
-    extern __shared__ uint32_t lh[];
-    const int c = blockIdx.x;
-    const int64_t n = part_count(n_host, d_n);
-    plan = plan_of_count(plan, n);
-    for (int b = threadIdx.x; b < bins; b += kHistThreads) lh[b] = 0;
-    __syncthreads();
-    const int64_t lo = chunk_begin(plan, c);
-    int64_t hi = chunk_begin(plan, c + 1);
-    if (hi > n) hi = n;
+// Adds the digits of items [lo, hi) to the block's LDS histogram (THREADS threads, all of them call it): a streaming read
+// with one LDS add per run of equal digits.  No barrier inside.
+template <int THREADS, class P>
+__device__ __forceinline__ void part_hist_range(const P& pol, int64_t lo, int64_t hi, uint32_t* lh) {
     constexpr int kBatch = 8;  // independent loads in flight per thread
     const int lane = threadIdx.x % kWave;
-    // the next batch is requested before the current one is counted (unconditional loads; past the end: the chunk's last
+    // the next batch is requested before the current one is counted (unconditional loads; past the end: the range's last
     // item, masked below)
     typename P::KeyT k[kBatch], kn[kBatch];
 #pragma unroll
@@ -198,15 +187,15 @@ part_hist_kernel(P pol, int n_host, const int* __restrict__ d_n, int bins, Chunk
     if (lo < hi) {  // uniform
 #pragma unroll
         for (int q = 0; q < kBatch; ++q) {
-            const int64_t i = lo + q * kHistThreads + threadIdx.x;
+            const int64_t i = lo + q * THREADS + threadIdx.x;
             kn[q] = pol.load_key(i < hi ? i : hi - 1);
         }
     }
-    for (int64_t base = lo; base < hi; base += static_cast<int64_t>(kHistThreads) * kBatch) {
+    for (int64_t base = lo; base < hi; base += static_cast<int64_t>(THREADS) * kBatch) {
 #pragma unroll
         for (int q = 0; q < kBatch; ++q) {
             k[q] = kn[q];
-            const int64_t i = base + static_cast<int64_t>(kHistThreads) * kBatch + q * kHistThreads + threadIdx.x;
+            const int64_t i = base + static_cast<int64_t>(THREADS) * kBatch + q * THREADS + threadIdx.x;
             kn[q] = pol.load_key(i < hi ? i : hi - 1);
         }
 #pragma unroll
@@ -214,7 +203,7 @@ part_hist_kernel(P pol, int n_host, const int* __restrict__ d_n, int bins, Chunk
             // The lanes of a wave hold consecutive items, so the valid lanes are a prefix of the wave.  After the
             // first pass equal digits arrive in runs (a popular key fills whole waves): one add per run of equal
             // digits instead of one per lane keeps such waves from serialising on a single LDS address.
-            const int64_t i = base + q * kHistThreads + threadIdx.x;
+            const int64_t i = base + q * THREADS + threadIdx.x;
             const bool valid = i < hi;
             const uint32_t d = valid ? pol.digit(k[q]) : 0xFFFFFFFFu;
             const uint32_t dprev = __shfl_up(d, 1, kWave);
@@ -228,6 +217,22 @@ part_hist_kernel(P pol, int n_host, const int* __restrict__ d_n, int bins, Chunk
             }
         }
     }
+}
+
+// It runs with kHistThreads threads per block, twice the scatter kernel's, to keep enough loads in flight with two blocks
+// per CU (0.21 -> 0.19 ms for three passes).
+template <class P>
+__global__ void __launch_bounds__(kHistThreads)
+part_hist_kernel(P pol, int n_host, const int* __restrict__ d_n, int bins, ChunkPlan plan, uint32_t* __restrict__ H) {
+    extern __shared__ uint32_t lh[];
+    const int c = blockIdx.x;
+    const int64_t n = part_count(n_host, d_n);
+    plan = plan_of_count(plan, n);
+    for (int b = threadIdx.x; b < bins; b += kHistThreads) lh[b] = 0;
+    __syncthreads();
+    int64_t hi = chunk_begin(plan, c + 1);
+    if (hi > n) hi = n;
+    part_hist_range<kHistThreads>(pol, chunk_begin(plan, c), hi, lh);
     __syncthreads();
     for (int b = threadIdx.x; b < bins; b += kHistThreads) H[static_cast<size_t>(c) * bins + b] = lh[b];
 }
@@ -276,6 +281,76 @@ part_colscan_kernel(uint32_t* __restrict__ H, int num_chunks, int bins, uint32_t
         }
         if (y == 0) bin_total[bin] = total;
     }
+}
+
+// Stable rank of every item among the items of its wave with the same digit.  The wave's IPT * 64 items are the tile's items
+// from w * IPT * 64 on, round i holds 64 consecutive ones; items from tile_count on do not take part.  Afterwards the wave's
+// counter of every bin holds its number of items.  cnt and the wave's mask table start cleared; the mask table ends cleared.
+template <int WAVES, int IPT>
+__device__ __forceinline__ void part_rank_items(const uint32_t (&d)[IPT], uint32_t (&r)[IPT], int nbits, int tile_count, int w, int lane,
+                                                uint16_t* cnt, unsigned long long* wmask) {
+    const unsigned long long lanebit = 1ull << lane;
+    const uint64_t lt = lanemask_lt();
+#pragma unroll
+    for (int i = 0; i < IPT; ++i) {
+        const int idx = w * (kWave * IPT) + i * kWave + lane;
+        const bool valid = idx < tile_count;
+        uint16_t* ctr = cnt + cnt_index<WAVES>(d[i], w);
+        uint64_t peers;
+        unsigned long long* slot = wmask + (d[i] & (kMaskSlots - 1));
+        // One digit in the whole wave (a popular key's run after the first pass, or few bins): every valid lane is a
+        // peer, no table needed; 64 lanes would also serialise on one slot.
+        const uint64_t vmask = __ballot(valid);
+        const bool one_digit = __ballot(valid && d[i] == static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(d[i]))) == vmask;
+        if (one_digit) {  // uniform
+            peers = vmask;
+        } else if (kMaskBits > 0) {
+            // every lane sets its bit in the slot of its digit's low bits, then reads the slot back: the lanes whose
+            // digits agree in those bits.  A wave's LDS operations execute in program order, so the read sees all 64
+            // ORs; the lowest peer clears the slot for the next round.
+            if (valid) atomicOr(slot, lanebit);
+            compiler_fence();
+            __builtin_amdgcn_wave_barrier();
+            peers = *slot;
+            if (nbits > kMaskBits) peers &= match_any(d[i] >> kMaskBits, nbits - kMaskBits, valid);
+        } else {
+            peers = match_any(d[i], nbits, valid);
+        }
+        const uint32_t pre = *ctr;
+        const uint64_t below = peers & lt;
+        r[i] = pre + __popcll(below);
+        compiler_fence();
+        __builtin_amdgcn_wave_barrier();
+        if (valid && below == 0) {
+            *ctr = static_cast<uint16_t>(pre + __popcll(peers));
+            if (kMaskBits > 0 && !one_digit) *slot = 0;
+        }
+        compiler_fence();
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// Turns one bin's per-wave counts into exclusive prefixes over the waves (wide reads, the prefixes in registers, wide
+// writes); returns the bin's total.  Prefixes stay below 65536: a tile has fewer items.
+template <int WAVES>
+__device__ __forceinline__ uint32_t part_bin_prefix(uint16_t* cnt, int b) {
+    CntRow* row = reinterpret_cast<CntRow*>(cnt + b * WAVES);
+    const uint32_t swz = cnt_swizzle<WAVES>(static_cast<uint32_t>(b));
+    uint32_t s = 0;
+#pragma unroll
+    for (int q = 0; q < WAVES / kCntRowWaves; ++q) {
+        CntRow x = row[q];
+        cnt_row_permute(x, swz);
+#pragma unroll
+        for (int j = 0; j < kCntRowWaves / 2; ++j) {
+            const uint32_t lo16 = x.w[j] & 0xffffu, hi16 = x.w[j] >> 16;
+            x.w[j] = s | ((s + lo16) << 16);
+            s += lo16 + hi16;
+        }
+        cnt_row_permute(x, swz);
+        row[q] = x;
+    }
+    return s;
 }
 
 // One exclusive scan of an int per thread across the block with a single barrier inside; `smem` (kPartWaves ints) must not
@@ -328,7 +403,6 @@ part_scatter_kernel(P pol, int n_host, const int* __restrict__ d_n, int bins, in
     // compiler-only fence keeps the accesses in program order; the wave's LDS operations execute in that order.
     uint16_t* cnt = reinterpret_cast<uint16_t*>(un);
     unsigned long long* wmask = reinterpret_cast<unsigned long long*>(un + part_cnt_bytes(bins)) + (threadIdx.x / kWave) * kMaskSlots;
-    const unsigned long long lanebit = 1ull << (threadIdx.x % kWave);
     unsigned char* st = ALIAS ? un : un + part_rank_bytes(bins);
     KeyT* skey = reinterpret_cast<KeyT*>(st);
     uint32_t* sval = reinterpret_cast<uint32_t*>(skey + kPartTile);
@@ -367,7 +441,6 @@ part_scatter_kernel(P pol, int n_host, const int* __restrict__ d_n, int bins, in
     const int64_t lo = chunk_begin(plan, c);
     int64_t hi = chunk_begin(plan, c + 1);
     if (hi > n) hi = n;
-    const uint64_t lt = lanemask_lt();
 
     // the items of the first tile; later tiles are fetched one iteration ahead and stay in flight across the LDS
     // barriers of the tile being ranked
@@ -411,66 +484,13 @@ part_scatter_kernel(P pol, int n_host, const int* __restrict__ d_n, int bins, in
             const int64_t at = tile_base + kPartTile + w * (kWave * kPartIPT) + i * kWave + lane;
             pol.load(at < hi ? at : last, kn[i], vn[i]);
         }
-        // stable rank of every item among the items of its wave with the same digit
-#pragma unroll
-        for (int i = 0; i < kPartIPT; ++i) {
-            const int idx = w * (kWave * kPartIPT) + i * kWave + lane;
-            const bool valid = idx < tile_count;
-            uint16_t* ctr = cnt + cnt_index(d[i], w);
-            uint64_t peers;
-            unsigned long long* slot = wmask + (d[i] & (kMaskSlots - 1));
-            // One digit in the whole wave (a popular key's run after the first pass, or few bins): every valid lane is a
-            // peer, no table needed; 64 lanes would also serialise on one slot.
-            const uint64_t vmask = __ballot(valid);
-            const bool one_digit = __ballot(valid && d[i] == static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(d[i]))) == vmask;
-            if (one_digit) {  // uniform
-                peers = vmask;
-            } else if (kMaskBits > 0) {
-                // every lane sets its bit in the slot of its digit's low bits, then reads the slot back: the lanes whose
-                // digits agree in those bits.  A wave's LDS operations execute in program order, so the read sees all 64
-                // ORs; the lowest peer clears the slot for the next round.
-                if (valid) atomicOr(slot, lanebit);
-                compiler_fence();
-                __builtin_amdgcn_wave_barrier();
-                peers = *slot;
-                if (nbits > kMaskBits) peers &= match_any(d[i] >> kMaskBits, nbits - kMaskBits, valid);
-            } else {
-                peers = match_any(d[i], nbits, valid);
-            }
-            const uint32_t pre = *ctr;
-            const uint64_t below = peers & lt;
-            r[i] = pre + __popcll(below);
-            compiler_fence();
-            __builtin_amdgcn_wave_barrier();
-            if (valid && below == 0) {
-                *ctr = static_cast<uint16_t>(pre + __popcll(peers));
-                if (kMaskBits > 0 && !one_digit) *slot = 0;
-            }
-            compiler_fence();
-            __builtin_amdgcn_wave_barrier();
-        }
+        part_rank_items<kPartWaves, kPartIPT>(d, r, nbits, tile_count, w, lane, cnt, wmask);
         lds_barrier();
-        // per bin: exclusive scan over the waves, total of the tile: one wide read, the prefixes in registers, one wide write
         int local = 0;
         for (int b = b0; b < b1; ++b) {
-            CntRow* row = reinterpret_cast<CntRow*>(cnt + b * kPartWaves);
-            const uint32_t swz = cnt_swizzle(static_cast<uint32_t>(b));
-            uint32_t s = 0;
-#pragma unroll
-            for (int q = 0; q < kPartWaves / kCntRowWaves; ++q) {
-                CntRow x = row[q];
-                cnt_row_permute(x, swz);
-#pragma unroll
-                for (int j = 0; j < kCntRowWaves / 2; ++j) {
-                    const uint32_t lo16 = x.w[j] & 0xffffu, hi16 = x.w[j] >> 16;
-                    x.w[j] = s | ((s + lo16) << 16);  // both prefixes stay below 65536 (a tile has fewer items)
-                    s += lo16 + hi16;
-                }
-                cnt_row_permute(x, swz);
-                row[q] = x;
-            }
-            delta[b] = s;
-            local += static_cast<int>(s);
+            const uint32_t t = part_bin_prefix<kPartWaves>(cnt, b);
+            delta[b] = t;
+            local += static_cast<int>(t);
         }
         int total;
         int run = part_block_scan(local, scan_tmp, &total);
@@ -485,7 +505,7 @@ part_scatter_kernel(P pol, int n_host, const int* __restrict__ d_n, int bins, in
 #pragma unroll
         for (int i = 0; i < kPartIPT; ++i) {
             const int idx = w * (kWave * kPartIPT) + i * kWave + lane;
-            r[i] += binstart[d[i]] + static_cast<uint32_t>(cnt[cnt_index(d[i], w)]);  // position inside the reordered tile
+            r[i] += binstart[d[i]] + static_cast<uint32_t>(cnt[cnt_index<kPartWaves>(d[i], w)]);  // position inside the reordered tile
             const uint32_t dst = delta[d[i]] + r[i];
             if (idx < tile_count && dst < static_cast<uint32_t>(n)) pol.placed(tile_base + idx, dst);
         }
@@ -529,32 +549,197 @@ part_scatter_kernel(P pol, int n_host, const int* __restrict__ d_n, int bins, in
     }
 }
 
+// ---- small inputs ------------------------------------------------------------------------------------------------
+//
+// A pass over few items is bound by its dependent launches (2-3 us each before any work) and by the latency of each one's
+// chain of loads, not by bytes, so it takes fewer of both:
+//   up to kSoloItems               ONE kernel.  Every block counts the digits of the whole input itself, those before its own
+//                                  tile apart, ranks its tile and writes it out.  It grows by 0.3 us per thousand items
+//   items x bins <= kSmallProduct  part_hist over at most kSmallChunks chunks, then the same kernel, which reads the histogram
+//                                  rows itself instead of having the columns scanned by a launch of their own
+// Items go straight to their places (no reordering through LDS): L2 holds the whole output.
+// np_dedup (sort and ranking), us, three launches a pass -> this: 17-bit keys (512 bins) 2 k 34 -> 18, 16 k 40 -> 30,
+// 64 k 41 -> 36, 256 k 45 -> 41, 512 k 49 -> 54; 20 bits (1024 bins) 128 k 45 -> 42, 256 k 47 -> 49; 22 bits (2048 bins)
+// 64 k 48 -> 44, 128 k 50 -> 50; one kernel against two: 16 k 30 / 35, 32 k 41 / 36, 64 k 60 / 36.
+constexpr int kSmallThreads = 1024;
+constexpr int kSmallWaves = kSmallThreads / kWave;
+constexpr int kSmallMaxBins = 2048;  // 16 two-byte counters per bin: 64 KB of LDS
+constexpr int kSmallChunks = 64;
+constexpr int kSoloIPT = 2;
+constexpr int kSoloTile = kSmallThreads * kSoloIPT;
+constexpr int kSoloItems = 24 * 1024;
+constexpr int64_t kSmallProduct = int64_t(1) << 27;
+
+inline size_t part_small_lds_bytes(int bins) {
+    const size_t words = (sizeof(uint32_t) * 2 * static_cast<size_t>(bins) + 64 + 15) / 16 * 16;
+    return words + sizeof(uint16_t) * kSmallWaves * static_cast<size_t>(bins) + sizeof(unsigned long long) * kSmallWaves * kMaskSlots;
+}
+
+template <class P, int IPT, bool SOLO>
+__global__ void __launch_bounds__(kSmallThreads)
+part_small_kernel(P pol, int n_host, const int* __restrict__ d_n, int bins, int nbits, ChunkPlan plan, const uint32_t* __restrict__ H,
+                  int32_t* __restrict__ totals_out /* nullable: [bins] */, int32_t* __restrict__ offsets_out /* nullable: [bins+1] */) {
+    constexpr int TILE = kSmallThreads * IPT;
+    using KeyT = typename P::KeyT;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    uint32_t* gofs = reinterpret_cast<uint32_t*>(smem_raw);  // items before this block's, later the next item's place, per bin
+    uint32_t* all = gofs + bins;                              // items per bin
+    int* scan_tmp = reinterpret_cast<int*>(all + bins);       // 16 ints
+    unsigned char* un = smem_raw + (sizeof(uint32_t) * 2 * static_cast<size_t>(bins) + 64 + 15) / 16 * 16;
+    uint16_t* cnt = reinterpret_cast<uint16_t*>(un);
+    const int tid = threadIdx.x, lane = tid % kWave, w = tid / kWave, c = blockIdx.x;
+    unsigned long long* wmask = reinterpret_cast<unsigned long long*>(un + sizeof(uint16_t) * kSmallWaves * static_cast<size_t>(bins)) + w * kMaskSlots;
+    const int64_t n = part_count(n_host, d_n);
+    plan = plan_of_count(plan, n);
+    const int64_t lo = SOLO ? static_cast<int64_t>(c) * TILE : chunk_begin(plan, c);
+    int64_t hi = SOLO ? lo + TILE : chunk_begin(plan, c + 1);
+    if (hi > n) hi = n;
+    if (lo >= hi && c != 0) return;  // uniform; block 0 stays for the totals
+
+    // the first tile's items are requested before anything else
+    KeyT kn[IPT];
+    uint32_t vn[IPT];
+    auto load_tile = [&](int64_t base) {
+#pragma unroll
+        for (int i = 0; i < IPT; ++i) {
+            const int64_t at = base + w * (kWave * IPT) + i * kWave + lane;
+            pol.load(at < hi ? at : hi - 1, kn[i], vn[i]);
+        }
+    };
+    if (lo < hi) load_tile(lo);
+    for (int b = tid; b < 2 * bins; b += kSmallThreads) gofs[b] = 0;
+    const int zn = static_cast<int>((sizeof(uint16_t) * kSmallWaves * static_cast<size_t>(bins) + sizeof(unsigned long long) * kSmallWaves * kMaskSlots) / 16);
+    for (int i = tid; i < zn; i += kSmallThreads) reinterpret_cast<uint4*>(un)[i] = make_uint4(0u, 0u, 0u, 0u);
+    lds_barrier();
+    if (SOLO) {
+        part_hist_range<kSmallThreads>(pol, 0, lo < n ? lo : n, gofs);
+        part_hist_range<kSmallThreads>(pol, lo < n ? lo : n, n, all);
+    } else {
+        const int ny = bins < kSmallThreads ? kSmallThreads / bins : 1;  // threads per bin, each takes every ny-th row
+        const int y = tid / bins;
+        if (y < ny || ny == 1) {
+            for (int b = ny == 1 ? tid : tid % bins; b < bins; b += ny == 1 ? kSmallThreads : bins) {
+                uint32_t before = 0, rest = 0;
+                for (int c0 = ny == 1 ? 0 : y; c0 < plan.num_chunks; c0 += 16 * ny) {
+                    uint32_t t[16];
+#pragma unroll
+                    for (int q = 0; q < 16; ++q) t[q] = c0 + q * ny < plan.num_chunks ? H[static_cast<size_t>(c0 + q * ny) * bins + b] : 0u;
+#pragma unroll
+                    for (int q = 0; q < 16; ++q) {
+                        if (c0 + q * ny < c) before += t[q];
+                        else rest += t[q];
+                    }
+                }
+                atomicAdd(&gofs[b], before);
+                atomicAdd(&all[b], rest);
+            }
+        }
+    }
+    lds_barrier();
+    const int bpt = (bins + kSmallThreads - 1) / kSmallThreads;
+    const int b0 = tid * bpt;
+    const int b1 = b0 + bpt < bins ? b0 + bpt : bins;
+    {
+        int local = 0;
+        for (int b = b0; b < b1; ++b) local += static_cast<int>(gofs[b] + all[b]);
+        int total;
+        int run = block_excl_scan<kSmallWaves>(local, scan_tmp, &total);
+        for (int b = b0; b < b1; ++b) {
+            const uint32_t before = gofs[b], t = before + all[b];
+            if (c == 0 && totals_out) totals_out[b] = static_cast<int32_t>(t);
+            if (c == 0 && offsets_out) offsets_out[b] = run;
+            gofs[b] = static_cast<uint32_t>(run) + before;
+            run += static_cast<int>(t);
+        }
+        if (c == 0 && offsets_out && tid == 0) offsets_out[bins] = total;
+    }
+    for (int64_t base = lo; base < hi; base += TILE) {
+        const int tile_count = hi - base < TILE ? static_cast<int>(hi - base) : TILE;
+        KeyT k[IPT];
+        uint32_t v[IPT], d[IPT], r[IPT];
+#pragma unroll
+        for (int i = 0; i < IPT; ++i) {
+            k[i] = kn[i];
+            v[i] = vn[i];
+            d[i] = w * (kWave * IPT) + i * kWave + lane < tile_count ? pol.digit(k[i]) : 0;
+        }
+        if (base + TILE < hi) load_tile(base + TILE);  // uniform
+        part_rank_items<kSmallWaves, IPT>(d, r, nbits, tile_count, w, lane, cnt, wmask);
+        lds_barrier();
+        uint32_t tile_total[2] = {0u, 0u};  // bins <= 2 * kSmallThreads
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            if (b0 + q < b1) tile_total[q] = part_bin_prefix<kSmallWaves>(cnt, b0 + q);
+        lds_barrier();
+#pragma unroll
+        for (int i = 0; i < IPT; ++i) {
+            const int idx = w * (kWave * IPT) + i * kWave + lane;
+            const uint32_t dst = gofs[d[i]] + static_cast<uint32_t>(cnt[cnt_index<kSmallWaves>(d[i], w)]) + r[i];
+            if (idx < tile_count && dst < static_cast<uint32_t>(n)) {  // dst always is; keeps a broken histogram from writing out of bounds
+                pol.store(dst, k[i], v[i]);
+                pol.placed(base + idx, dst);
+            }
+        }
+        if (base + TILE < hi) {  // uniform: another tile follows
+            lds_barrier();
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                if (b0 + q < b1) gofs[b0 + q] += tile_total[q];
+            const int zc = static_cast<int>(sizeof(uint16_t) * kSmallWaves * static_cast<size_t>(bins) / 16);
+            for (int i = tid; i < zc; i += kSmallThreads) reinterpret_cast<uint4*>(un)[i] = make_uint4(0u, 0u, 0u, 0u);
+            lds_barrier();
+        }
+    }
+}
+
+// Above the default dynamic-LDS allowance: opt in, once per device, kernel and size (a failure shows up as a failed launch);
+// later calls, e.g. while a caller records a graph, then enqueue kernels only.  `granted` belongs to one kernel.
+inline void allow_dynamic_lds(const void* fn, size_t lds, std::atomic<int>* granted) {
+    if (lds <= 48 * 1024) return;
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    const bool tracked = dev >= 0 && dev < kMaxDevices;
+    if (!tracked || granted[dev].load(std::memory_order_relaxed) < static_cast<int>(lds)) {
+        (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+        if (tracked) granted[dev].store(static_cast<int>(lds), std::memory_order_relaxed);
+    }
+}
+
 // Enqueue one partition pass over n_host items, or over min(*d_n, n_host) items when d_n is given.  H needs
 // part_hist_elems() words, bin_total needs `bins` words.
 template <class P>
 inline void run_partition_pass(const P& pol, int n_host, const int* d_n, int bins, int nbits, const ChunkPlan& plan,
                                uint32_t* H, uint32_t* bin_total, int32_t* totals_out, int32_t* offsets_out,
                                hipStream_t stream, const char* tag_hist, const char* tag_scan, const char* tag_scatter) {
+    if (bins <= kSmallMaxBins && (n_host <= kSoloItems || static_cast<int64_t>(n_host) * bins <= kSmallProduct)) {
+        static std::atomic<int> granted_small[2][kMaxDevices];
+        const size_t lds = part_small_lds_bytes(bins);
+        if (n_host <= kSoloItems) {
+            allow_dynamic_lds(reinterpret_cast<const void*>(part_small_kernel<P, kSoloIPT, true>), lds, granted_small[0]);
+            const int blocks = n_host > kSoloTile ? (n_host + kSoloTile - 1) / kSoloTile : 1;
+            NP_LAUNCH(tag_scatter, (part_small_kernel<P, kSoloIPT, true>), dim3(blocks), dim3(kSmallThreads), lds, stream, pol, n_host, d_n,
+                      bins, nbits, plan, H, totals_out, offsets_out);
+            return;
+        }
+        constexpr int kIPT = kPartTile / kSmallThreads;
+        ChunkPlan few = plan;
+        if (few.num_chunks > kSmallChunks) few.num_chunks = kSmallChunks;
+        allow_dynamic_lds(reinterpret_cast<const void*>(part_small_kernel<P, kIPT, false>), lds, granted_small[1]);
+        NP_LAUNCH(tag_hist, part_hist_kernel<P>, dim3(few.num_chunks), dim3(kHistThreads), sizeof(uint32_t) * bins, stream, pol, n_host,
+                  d_n, bins, few, H);
+        NP_LAUNCH(tag_scatter, (part_small_kernel<P, kIPT, false>), dim3(few.num_chunks), dim3(kSmallThreads), lds, stream, pol, n_host, d_n,
+                  bins, nbits, few, H, totals_out, offsets_out);
+        return;
+    }
     NP_LAUNCH(tag_hist, part_hist_kernel<P>, dim3(plan.num_chunks), dim3(kHistThreads), sizeof(uint32_t) * bins, stream,
               pol, n_host, d_n, bins, plan, H);
     NP_LAUNCH(tag_scan, part_colscan_kernel<kColscanThreads>, dim3((bins + kWave - 1) / kWave), dim3(kColscanThreads), 0, stream, H,
               plan.num_chunks, bins, bin_total);
     const size_t lds = part_scatter_lds_bytes<typename P::KeyT>(bins, P::kStageDigit);
     const bool aliased = part_stage_aliased<typename P::KeyT>(bins, P::kStageDigit);
-    const void* fn = aliased ? reinterpret_cast<const void*>(part_scatter_kernel<P, true>)
-                             : reinterpret_cast<const void*>(part_scatter_kernel<P, false>);
-    if (lds > 48 * 1024) {
-        // above the default dynamic-LDS allowance: opt in, once per device, kernel and size (a failure shows up as a failed
-        // launch); later calls, e.g. while a caller records a graph, then enqueue kernels only
-        static std::atomic<int> granted[2][kMaxDevices];
-        int dev = 0;
-        (void)hipGetDevice(&dev);
-        const bool tracked = dev >= 0 && dev < kMaxDevices;
-        if (!tracked || granted[aliased][dev].load(std::memory_order_relaxed) < static_cast<int>(lds)) {
-            (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
-            if (tracked) granted[aliased][dev].store(static_cast<int>(lds), std::memory_order_relaxed);
-        }
-    }
+    static std::atomic<int> granted[2][kMaxDevices];
+    allow_dynamic_lds(aliased ? reinterpret_cast<const void*>(part_scatter_kernel<P, true>)
+                              : reinterpret_cast<const void*>(part_scatter_kernel<P, false>), lds, granted[aliased]);
     if (aliased)
         NP_LAUNCH(tag_scatter, (part_scatter_kernel<P, true>), dim3(plan.num_chunks), dim3(kPartThreads), lds, stream, pol, n_host,
                   d_n, bins, nbits, plan, H, bin_total, totals_out, offsets_out);
