@@ -61,32 +61,91 @@ struct __align__(16) BagMapEntry {
     int32_t start0;   // bag_offsets[bag0]
 };
 
-__device__ __forceinline__ void bagmap_entry(int w, const int32_t* __restrict__ bag_offsets, int num_bags, int n,
-                                              BagMapEntry* __restrict__ map) {
-    const int64_t base64 = static_cast<int64_t>(w) * 64;
-    if (base64 >= n) return;
+// First index in [0, count) whose value is at least x, count if there is none; values ascend.  G consecutive lanes search
+// together, G - 1 pivots a round (each round is one load latency: log_G instead of log_2 of them).
+template <int G>
+__device__ __forceinline__ int group_lower_bound(const int32_t* __restrict__ v, int count, int x) {
+    static_assert(G >= 2, "one pivot a round would be a linear walk");
+    const int r = __lane_id() & (G - 1), g0 = __lane_id() & ~(G - 1);
+    const uint64_t gmask = (G == 64 ? ~0ull : ((1ull << (G & 63)) - 1ull)) << g0;
+    int lo = 0, hi = count;  // the answer is in [lo, hi]
+    while (__ballot(lo < hi) & gmask) {  // uniform inside the group
+        const int64_t len = hi - lo;
+        const int at = lo + static_cast<int>(len * r / G);  // lane 0: lo itself; strictly inside [lo, hi)
+        const bool below = lo < hi && v[at] < x;
+        const int k = __popcll(__ballot(below) & gmask);  // pivots 0 .. k - 1 are below x
+        if (lo < hi) {
+            if (k == 0) {
+                hi = lo;
+            } else {
+                const int nlo = lo + static_cast<int>(len * (k - 1) / G) + 1;
+                if (k < G) hi = lo + static_cast<int>(len * k / G);
+                lo = nlo < hi ? nlo : hi;
+            }
+        }
+    }
+    return lo;
+}
+
+// Map entries of WORDS blocks of 64 lookups by one block of 256 threads: the bags that start there are read once, coalesced,
+// and mark their start bit in LDS; how many start before a block of lookups is a prefix sum over the per-block counts.  One
+// thread per entry, walking the bags of its 64 lookups one load after the other, took 24 us for 0.5 M lookups that are bags of
+// their own; this takes 8.
+template <int WORDS>
+__device__ __forceinline__ void bagmap_block(int blk, const int32_t* __restrict__ bag_offsets, int num_bags, int n,
+                                             BagMapEntry* __restrict__ map) {
+    static_assert(WORDS <= 256, "one thread per entry");
+    __shared__ unsigned long long starts[WORDS];
+    __shared__ int on_first[WORDS], again[WORDS];  // bags that start on the block's first lookup; that start where another does
+    __shared__ int first_bag, scan_tmp[16];
+    const int t = threadIdx.x;
+    const int64_t base64 = static_cast<int64_t>(blk) * (WORDS * 64);
+    if (base64 >= n) return;  // uniform
     const int base = static_cast<int>(base64);
-    int lo = 0, hi = num_bags;  // last bag in [lo, hi) that starts at or before base; it is non-empty and holds base
-    while (hi - lo > 1) {
-        const int mid = lo + (hi - lo) / 2;
-        if (bag_offsets[mid] <= base) lo = mid;
-        else hi = mid;
+    const int end = n - base < WORDS * 64 ? n : base + WORDS * 64;
+    if (t < WORDS) {
+        starts[t] = 0;
+        on_first[t] = again[t] = 0;
     }
-    const int last = n - 1 - base < 63 ? n - 1 : base + 63;
-    uint64_t bits = 0;
-    bool twice = false;
-    for (int b = lo + 1; b < num_bags; ++b) {
-        const int o = bag_offsets[b];
-        if (o > last) break;
-        const uint64_t m = 1ull << (o - base);
-        twice |= (bits & m) != 0;
-        bits |= m;
+    if (t < kWave) {
+        const int b = group_lower_bound<kWave>(bag_offsets, num_bags, base);
+        if (t == 0) first_bag = b;
     }
-    BagMapEntry e;
-    e.starts = bits;
-    e.bag0 = twice ? (lo | static_cast<int32_t>(0x80000000u)) : lo;
-    e.start0 = bag_offsets[lo];
-    map[w] = e;
+    __syncthreads();
+    const int b0 = first_bag;  // bags before it start before `base`
+    for (int64_t chunk = b0; chunk < num_bags; chunk += 4 * 256) {
+        int o[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int64_t b = chunk + q * 256 + t;
+            o[q] = bag_offsets[b < num_bags ? b : num_bags];  // bag_offsets[num_bags] = n: never below `end`
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (o[q] < end) {
+                const int wd = (o[q] - base) >> 6, k = (o[q] - base) & 63;
+                if (k == 0) {
+                    atomicAdd(&on_first[wd], 1);
+                } else {
+                    const unsigned long long m = 1ull << k;
+                    if (atomicOr(&starts[wd], m) & m) atomicAdd(&again[wd], 1);
+                }
+            }
+        }
+        if (o[3] >= end) break;  // this thread's later bags start further out still
+    }
+    __syncthreads();
+    const int mine = t < WORDS ? on_first[t] + __popcll(starts[t]) + again[t] : 0;
+    int total;
+    const int before = block_excl_scan<256 / kWave>(mine, scan_tmp, &total);
+    if (t < WORDS && base + t * 64 < end) {
+        const int bag = b0 + before + on_first[t] - 1;  // last bag that starts at or before the block's first lookup
+        BagMapEntry e;
+        e.starts = starts[t];
+        e.bag0 = again[t] ? (bag | static_cast<int32_t>(0x80000000u)) : bag;
+        e.start0 = bag_offsets[bag];
+        map[(base >> 6) + t] = e;
+    }
 }
 
 // Bag of lookup j and the first lookup of that bag, from the map entry of j's block of 64 lookups.
@@ -108,29 +167,29 @@ __device__ __forceinline__ void bag_of_lookup(const BagMapEntry* __restrict__ ma
     bag_from_entry(map[j >> 6], bag_offsets, j, bag, start);
 }
 
-__device__ __forceinline__ void tile_first_segment(int t, const int32_t* __restrict__ occ_offsets, const int32_t* __restrict__ d_num_unique,
+// First segment of 256 / LANES tiles per block: the last u with occ_offsets[u] <= the tile's first position.
+template <int LANES>
+__device__ __forceinline__ void tile_first_segment(int blk, const int32_t* __restrict__ occ_offsets, const int32_t* __restrict__ d_num_unique,
                                                    int n, int num_tiles, int32_t* __restrict__ tile_seg0) {
-    if (t >= num_tiles) return;
-    const int pos = t * kBwdTile;
-    int lo = 0, hi = device_count(d_num_unique, n);  // U <= n; the answer is the last u in [lo, hi) with occ_offsets[u] <= pos
-    while (hi - lo > 1) {
-        const int mid = lo + (hi - lo) / 2;
-        if (occ_offsets[mid] <= pos) lo = mid;
-        else hi = mid;
-    }
-    tile_seg0[t] = lo;
+    const int t = blk * (256 / LANES) + threadIdx.x / LANES;
+    if (t >= num_tiles) return;  // whole groups leave together
+    const int U = device_count(d_num_unique, n);  // U <= n
+    const int u = group_lower_bound<LANES>(occ_offsets, U, t * kBwdTile + 1) - 1;
+    if ((threadIdx.x & (LANES - 1)) == 0) tile_seg0[t] = u < 0 ? 0 : u;
 }
 
 // The two preparations that depend on nothing but the batch's index arrays, in one launch: the first map_blocks blocks
-// write the bag map (one entry per thread), the rest find the first segment of every tile (one tile per thread).
+// write the bag map, the rest find the first segment of every tile.  Small batches are bound by the searches' latency (many
+// lanes per search, many blocks), large ones by the loads the searches make: see bwd_prepare_launch.
+template <int WORDS, int LANES>
 __global__ void __launch_bounds__(256)
 bwd_prepare_kernel(const int32_t* __restrict__ bag_offsets, int num_bags, int n, BagMapEntry* __restrict__ map, int map_blocks,
                    const int32_t* __restrict__ occ_offsets, const int32_t* __restrict__ d_num_unique, int num_tiles,
                    int32_t* __restrict__ tile_seg0) {
     if (static_cast<int>(blockIdx.x) < map_blocks)
-        bagmap_entry(blockIdx.x * 256 + threadIdx.x, bag_offsets, num_bags, n, map);
+        bagmap_block<WORDS>(blockIdx.x, bag_offsets, num_bags, n, map);
     else
-        tile_first_segment((blockIdx.x - map_blocks) * 256 + threadIdx.x, occ_offsets, d_num_unique, n, num_tiles, tile_seg0);
+        tile_first_segment<LANES>(blockIdx.x - map_blocks, occ_offsets, d_num_unique, n, num_tiles, tile_seg0);
 }
 
 // Block -> tile of bwd_main: die x (blocks x, x + 8, ...) first runs its contiguous share of the locality-ordered tiles,
@@ -960,9 +1019,19 @@ inline BwdPlan bwd_plan(const BwdArgs& a) {
 
 // Everything that depends on the batch's index arrays alone (bag offsets, occurrence offsets), not on dY.
 inline void bwd_prepare_launch(const BwdArgs& a, const BwdPlan& P) {
-    const int map_blocks = (P.map_entries + 255) / 256, seg_blocks = (P.num_tiles + 255) / 256;
-    NP_LAUNCH("bwd_prepare", bwd_prepare_kernel, dim3(map_blocks + seg_blocks), dim3(256), 0, a.stream, a.bag_offsets, a.num_bags,
-              a.n, P.bagmap, map_blocks, a.occ_offsets, a.d_num_unique, P.num_tiles, P.tile_seg0);
+#define NP_BWD_PREPARE(W_, L_)                                                                                                \
+    do {                                                                                                                     \
+        const int map_blocks = (P.map_entries + W_ - 1) / W_;                                                                \
+        const int seg_blocks = static_cast<int>((P.num_tiles * static_cast<int64_t>(L_) + 255) / 256);                       \
+        NP_LAUNCH("bwd_prepare", (bwd_prepare_kernel<W_, L_>), dim3(map_blocks + seg_blocks), dim3(256), 0, a.stream,        \
+                  a.bag_offsets, a.num_bags, a.n, P.bagmap, map_blocks, a.occ_offsets, a.d_num_unique, P.num_tiles,          \
+                  P.tile_seg0);                                                                                              \
+    } while (0)
+    // 32 entries per block and 16 lanes per search where latency counts: 0.2 M lookups 10.7 -> 4.6 us, 1.7 M 10.9 -> 6.5,
+    // 0.5 M one-lookup bags 23.7 -> 7.9.  256 and 8 above: 42 M lookups 38 -> 33 us (51 with the small form), 9.8 M 10 -> 7.5.
+    if (a.n < (4 << 20)) NP_BWD_PREPARE(32, 16);
+    else NP_BWD_PREPARE(256, 8);
+#undef NP_BWD_PREPARE
     if (P.ordered) {
         TileOrderPolicy pol{P.tile_seg0, a.occ_offsets, P.order, a.n};
         run_partition_pass(pol, P.num_tiles, nullptr, kOrderBuckets + 1, 11, P.oplan, P.oH, P.obin, nullptr, P.order_offsets,
