@@ -22,7 +22,17 @@ __device__ __forceinline__ void store_words(float* p, const float4& a) { store_w
 
 __device__ __forceinline__ void store_words(uint16_t* p, const float4& a) { store_word_stream(p, 0, a); }
 
-constexpr int kFwdUnroll = 4;
+// Table rows a lane group of the pooling kernels keeps in flight (UN).  More of them shorten the walk of a long bag, and cost
+// short bags instructions and everyone registers (16: half the waves per CU), so the host chooses by the mean bag length:
+//   below 8          4     0.43 M bags of 4, dim 64: 57 us, 62 with 8, 79 with 16
+//   8 and more       8     65 k bags of 32: 50 -> 40 us; 1.3 M bags of 8 on a bf16 table: 204 -> 195
+//   32 and more     16     where the bags are too few to fill the GPU (four waves per CU), so that the walk's latency is all
+//                          there is: 8000 bags of 64, dim 64: 24.5 -> 19.9 (8) -> 16.6 us; 800, dim 256: 18.5 -> 16.0 -> 14.4
+inline int fwd_rows_in_flight(int num_bags, int n, int lanes) {
+    if (n < 8 * static_cast<int64_t>(num_bags)) return 4;
+    if (n >= 32 * static_cast<int64_t>(num_bags) && static_cast<int64_t>(num_bags) * lanes <= 256 * 1024) return 16;
+    return 8;
+}
 
 // Table row read by lookup j: list_keys[idx[j]]; without idx the list has one entry per lookup; without list_keys the
 // slot itself is the row (pooling straight from a buffer of received rows).
@@ -31,7 +41,7 @@ __device__ __forceinline__ int64_t lookup_row(const int64_t* __restrict__ list_k
     return list_keys ? list_keys[slot] : slot;
 }
 
-template <int LPR, int NV, bool MEAN, typename OutT, typename TabT>
+template <int LPR, int NV, int UNROLL, bool MEAN, typename OutT, typename TabT>
 __global__ void __launch_bounds__(256)
 fwd_pool_kernel(const TabT* __restrict__ table, int dim, const int64_t* __restrict__ list_keys, const int32_t* __restrict__ idx,
                 const int32_t* __restrict__ bag_offsets, int num_bags, OutT* __restrict__ out) {
@@ -45,19 +55,21 @@ fwd_pool_kernel(const TabT* __restrict__ table, int dim, const int64_t* __restri
 #pragma unroll
     for (int v = 0; v < NV; ++v) acc[v] = make_float4(0.f, 0.f, 0.f, 0.f);
 
+    constexpr int UN = UNROLL < LPR ? UNROLL : LPR;
     const int gl = __lane_id() & ~(LPR - 1);  // first lane of this group
+    // one lane per lookup: slot, key and the byte offset of the row (the 64-bit multiply happens here, once per lookup,
+    // instead of in every lane of the walk below), requested one strip of lookups ahead of the rows
+    auto strip_row = [&](int j) -> int64_t { return j < hi ? lookup_row(list_keys, idx, j) : 0; };
+    int64_t next_row = strip_row(lo + r);
     for (int base = lo; base < hi; base += LPR) {
-        const int j = base + r;
-        // one lane per lookup: slot, key and the byte offset of the row (the 64-bit multiply happens here, once
-        // per lookup, instead of in every lane of the walk below)
-        int64_t row_off = 0;
-        if (j < hi) row_off = lookup_row(list_keys, idx, j) * static_cast<int64_t>(dim) * static_cast<int64_t>(sizeof(TabT));
+        const int64_t row_off = next_row * static_cast<int64_t>(dim) * static_cast<int64_t>(sizeof(TabT));
+        if (base + LPR < hi) next_row = strip_row(base + LPR + r);
         const int off_lo = static_cast<int>(row_off & 0xFFFFFFFFll), off_hi = static_cast<int>(row_off >> 32);
         const int cnt = hi - base < LPR ? hi - base : LPR;
-        for (int k0 = 0; k0 < cnt; k0 += kFwdUnroll) {
-            float4 x[kFwdUnroll][NV];
+        for (int k0 = 0; k0 < cnt; k0 += UN) {
+            float4 x[UN][NV];
 #pragma unroll
-            for (int q = 0; q < kFwdUnroll; ++q) {
+            for (int q = 0; q < UN; ++q) {
                 const bool on = k0 + q < cnt;  // uniform inside the group; k0 + q < LPR always
                 const uint32_t lo32 = static_cast<uint32_t>(__shfl(off_lo, gl + k0 + q, kWave));
                 const uint32_t hi32 = static_cast<uint32_t>(__shfl(off_hi, gl + k0 + q, kWave));
@@ -70,7 +82,7 @@ fwd_pool_kernel(const TabT* __restrict__ table, int dim, const int64_t* __restri
                 }
             }
 #pragma unroll
-            for (int q = 0; q < kFwdUnroll; ++q) {
+            for (int q = 0; q < UN; ++q) {
 #pragma unroll
                 for (int v = 0; v < NV; ++v) {  // rows that were not loaded are zeros
                     acc[v].x += x[q][v].x;
@@ -115,7 +127,7 @@ __device__ __forceinline__ void widen8(const uint16_t*, const uint4& u, float4& 
                     __uint_as_float(u.w & 0xFFFF0000u));
 }
 
-template <int L8, int NV8, bool MEAN, typename OutT, typename TabT>
+template <int L8, int NV8, int UNROLL, bool MEAN, typename OutT, typename TabT>
 __global__ void __launch_bounds__(256)
 fwd_pool_x8_kernel(const TabT* __restrict__ table, int dim, const int64_t* __restrict__ list_keys,
                        const int32_t* __restrict__ idx, const int32_t* __restrict__ bag_offsets, int num_bags, OutT* __restrict__ out) {
@@ -128,18 +140,20 @@ fwd_pool_x8_kernel(const TabT* __restrict__ table, int dim, const int64_t* __res
     float4 acc[NV8][2];
 #pragma unroll
     for (int v = 0; v < NV8; ++v) acc[v][0] = acc[v][1] = make_float4(0.f, 0.f, 0.f, 0.f);
+    constexpr int UN = UNROLL < L8 ? UNROLL : L8;
     const int gl = __lane_id() & ~(L8 - 1);
+    auto strip_row = [&](int j) -> int64_t { return j < hi ? lookup_row(list_keys, idx, j) : 0; };
+    int64_t next_row = strip_row(lo + r);
     for (int base = lo; base < hi; base += L8) {
-        const int j = base + r;
-        int64_t row_off = 0;
-        if (j < hi) row_off = lookup_row(list_keys, idx, j) * static_cast<int64_t>(dim) * 2;
+        const int64_t row_off = next_row * static_cast<int64_t>(dim) * 2;
+        if (base + L8 < hi) next_row = strip_row(base + L8 + r);
         const int off_lo = static_cast<int>(row_off & 0xFFFFFFFFll), off_hi = static_cast<int>(row_off >> 32);
         const int cnt = hi - base < L8 ? hi - base : L8;
-        for (int k0 = 0; k0 < cnt; k0 += kFwdUnroll) {
-            uint4 x[kFwdUnroll][NV8];
+        for (int k0 = 0; k0 < cnt; k0 += UN) {
+            uint4 x[UN][NV8];
 #pragma unroll
-            for (int q = 0; q < kFwdUnroll; ++q) {
-                const bool on = k0 + q < cnt;  // uniform inside the group; k0 + q < L8 always (L8 >= kFwdUnroll)
+            for (int q = 0; q < UN; ++q) {
+                const bool on = k0 + q < cnt;  // uniform inside the group; k0 + q < L8 always (L8 >= UN)
                 const uint32_t lo32 = static_cast<uint32_t>(__shfl(off_lo, gl + k0 + q, kWave));
                 const uint32_t hi32 = static_cast<uint32_t>(__shfl(off_hi, gl + k0 + q, kWave));
                 const uint4* src = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(table) +
@@ -151,7 +165,7 @@ fwd_pool_x8_kernel(const TabT* __restrict__ table, int dim, const int64_t* __res
                 }
             }
 #pragma unroll
-            for (int q = 0; q < kFwdUnroll; ++q) {
+            for (int q = 0; q < UN; ++q) {
 #pragma unroll
                 for (int v = 0; v < NV8; ++v) {  // rows that were not loaded are zeros
                     float4 a, c;
@@ -189,27 +203,55 @@ fwd_pool_x8_kernel(const TabT* __restrict__ table, int dim, const int64_t* __res
     }
 }
 
-template <int L8, int NV8, typename TabT>
-void fwd_pool_x8_launch(const TabT* table, int dim, const int64_t* list_keys, const int32_t* idx, const int32_t* bag_offsets,
-                            int num_bags, int mode, int out_dtype, void* out, hipStream_t stream) {
-    constexpr int GPB = 256 / L8;
-    const unsigned grid = static_cast<unsigned>((static_cast<int64_t>(num_bags) + GPB - 1) / GPB);
-    const bool mean = mode == NP_POOL_MEAN;
-    if (out_dtype == NP_BF16) {
-        if (mean)
-            NP_LAUNCH("fwd_pool", (fwd_pool_x8_kernel<L8, NV8, true, uint16_t, TabT>), dim3(grid), dim3(256), 0, stream, table, dim,
-                      list_keys, idx, bag_offsets, num_bags, static_cast<uint16_t*>(out));
-        else
-            NP_LAUNCH("fwd_pool", (fwd_pool_x8_kernel<L8, NV8, false, uint16_t, TabT>), dim3(grid), dim3(256), 0, stream, table, dim,
-                      list_keys, idx, bag_offsets, num_bags, static_cast<uint16_t*>(out));
+struct FwdArgs {
+    const void* table;
+    int dim;
+    const int64_t* list_keys;
+    const int32_t* d_num_list;
+    int cap;
+    const int32_t* idx;
+    const int32_t* bag_offsets;
+    int num_bags, n, mode, max_len, out_dtype;
+    void* out;
+    void* rows_out;
+    hipStream_t stream;
+};
+
+// X8: the lanes own eight elements of a 16-bit table each (fwd_pool_x8_kernel), otherwise four of any table.
+template <int LANES, int NV, int UNROLL, bool X8, bool MEAN, typename OutT, typename TabT>
+void fwd_pool_launch(const FwdArgs& a) {
+    constexpr int GPB = 256 / LANES;
+    const dim3 grid(static_cast<unsigned>((static_cast<int64_t>(a.num_bags) + GPB - 1) / GPB));
+    const TabT* table = static_cast<const TabT*>(a.table);
+    OutT* out = static_cast<OutT*>(a.out);
+    if constexpr (X8)
+        NP_LAUNCH("fwd_pool", (fwd_pool_x8_kernel<LANES, NV, UNROLL, MEAN, OutT, TabT>), grid, dim3(256), 0, a.stream, table, a.dim,
+                  a.list_keys, a.idx, a.bag_offsets, a.num_bags, out);
+    else
+        NP_LAUNCH("fwd_pool", (fwd_pool_kernel<LANES, NV, UNROLL, MEAN, OutT, TabT>), grid, dim3(256), 0, a.stream, table, a.dim,
+                  a.list_keys, a.idx, a.bag_offsets, a.num_bags, out);
+}
+
+template <int LANES, int NV, int UNROLL, bool X8, typename TabT>
+void fwd_pool_types(const FwdArgs& a) {
+    const bool mean = a.mode == NP_POOL_MEAN;
+    if (a.out_dtype == NP_BF16) {
+        if (mean) fwd_pool_launch<LANES, NV, UNROLL, X8, true, uint16_t, TabT>(a);
+        else fwd_pool_launch<LANES, NV, UNROLL, X8, false, uint16_t, TabT>(a);
     } else {
-        if (mean)
-            NP_LAUNCH("fwd_pool", (fwd_pool_x8_kernel<L8, NV8, true, float, TabT>), dim3(grid), dim3(256), 0, stream, table, dim,
-                      list_keys, idx, bag_offsets, num_bags, static_cast<float*>(out));
-        else
-            NP_LAUNCH("fwd_pool", (fwd_pool_x8_kernel<L8, NV8, false, float, TabT>), dim3(grid), dim3(256), 0, stream, table, dim,
-                      list_keys, idx, bag_offsets, num_bags, static_cast<float*>(out));
+        if (mean) fwd_pool_launch<LANES, NV, UNROLL, X8, true, float, TabT>(a);
+        else fwd_pool_launch<LANES, NV, UNROLL, X8, false, float, TabT>(a);
     }
+}
+
+template <int LANES, int NV, bool X8, typename TabT>
+void fwd_pool(const FwdArgs& a) {
+    if constexpr (NV == 1) {  // wider rows have several words per lane and row in flight already
+        const int rows = fwd_rows_in_flight(a.num_bags, a.n, LANES);
+        if (rows == 16) return fwd_pool_types<LANES, NV, 16, X8, TabT>(a);
+        if (rows == 8) return fwd_pool_types<LANES, NV, 8, X8, TabT>(a);
+    }
+    fwd_pool_types<LANES, NV, 4, X8, TabT>(a);
 }
 
 #ifndef NP_SEQ_PER_GROUP
@@ -388,20 +430,6 @@ fwd_rows_kernel(const TabT* __restrict__ table, int dim, const int64_t* __restri
     }
 }
 
-struct FwdArgs {
-    const void* table;
-    int dim;
-    const int64_t* list_keys;
-    const int32_t* d_num_list;
-    int cap;
-    const int32_t* idx;
-    const int32_t* bag_offsets;
-    int num_bags, mode, max_len, out_dtype;
-    void* out;
-    void* rows_out;
-    hipStream_t stream;
-};
-
 template <int LPR, int NV, typename TabT>
 void fwd_launch(const FwdArgs& a) {
     constexpr int GPB = 256 / LPR;
@@ -419,23 +447,7 @@ void fwd_launch(const FwdArgs& a) {
                 NP_LAUNCH("fwd_seq", (fwd_seq_kernel<LPR, NV, float, TabT>), dim3(grid), dim3(256), 0, a.stream, table, a.dim,
                           a.list_keys, a.idx, a.bag_offsets, a.num_bags, a.max_len, static_cast<float*>(a.out));
         } else {
-            const unsigned grid = static_cast<unsigned>((static_cast<int64_t>(a.num_bags) + GPB - 1) / GPB);
-            const bool mean = a.mode == NP_POOL_MEAN;
-            if (a.out_dtype == NP_BF16) {
-                if (mean)
-                    NP_LAUNCH("fwd_pool", (fwd_pool_kernel<LPR, NV, true, uint16_t, TabT>), dim3(grid), dim3(256), 0, a.stream, table,
-                              a.dim, a.list_keys, a.idx, a.bag_offsets, a.num_bags, static_cast<uint16_t*>(a.out));
-                else
-                    NP_LAUNCH("fwd_pool", (fwd_pool_kernel<LPR, NV, false, uint16_t, TabT>), dim3(grid), dim3(256), 0, a.stream, table,
-                              a.dim, a.list_keys, a.idx, a.bag_offsets, a.num_bags, static_cast<uint16_t*>(a.out));
-            } else {
-                if (mean)
-                    NP_LAUNCH("fwd_pool", (fwd_pool_kernel<LPR, NV, true, float, TabT>), dim3(grid), dim3(256), 0, a.stream, table,
-                              a.dim, a.list_keys, a.idx, a.bag_offsets, a.num_bags, static_cast<float*>(a.out));
-                else
-                    NP_LAUNCH("fwd_pool", (fwd_pool_kernel<LPR, NV, false, float, TabT>), dim3(grid), dim3(256), 0, a.stream, table,
-                              a.dim, a.list_keys, a.idx, a.bag_offsets, a.num_bags, static_cast<float*>(a.out));
-            }
+            fwd_pool<LPR, NV, false, TabT>(a);
         }
     }
     if (a.rows_out && a.cap > 0) {
@@ -464,12 +476,12 @@ template <typename TabT>
 void fwd_16bit(FwdArgs a, const TabT* t) {
     if (a.mode != NP_SEQ && a.dim % 8 == 0 && a.dim >= 32 && a.num_bags > 0 && aligned(t, 16)) {
         const int chunks = a.dim / 8;
-        if (chunks <= 4) fwd_pool_x8_launch<4, 1>(t, a.dim, a.list_keys, a.idx, a.bag_offsets, a.num_bags, a.mode, a.out_dtype, a.out, a.stream);
-        else if (chunks <= 8) fwd_pool_x8_launch<8, 1>(t, a.dim, a.list_keys, a.idx, a.bag_offsets, a.num_bags, a.mode, a.out_dtype, a.out, a.stream);
-        else if (chunks <= 16) fwd_pool_x8_launch<16, 1>(t, a.dim, a.list_keys, a.idx, a.bag_offsets, a.num_bags, a.mode, a.out_dtype, a.out, a.stream);
-        else if (chunks <= 32) fwd_pool_x8_launch<32, 1>(t, a.dim, a.list_keys, a.idx, a.bag_offsets, a.num_bags, a.mode, a.out_dtype, a.out, a.stream);
-        else if (chunks <= 64) fwd_pool_x8_launch<64, 1>(t, a.dim, a.list_keys, a.idx, a.bag_offsets, a.num_bags, a.mode, a.out_dtype, a.out, a.stream);
-        else fwd_pool_x8_launch<64, 2>(t, a.dim, a.list_keys, a.idx, a.bag_offsets, a.num_bags, a.mode, a.out_dtype, a.out, a.stream);
+        if (chunks <= 4) fwd_pool<4, 1, true, TabT>(a);
+        else if (chunks <= 8) fwd_pool<8, 1, true, TabT>(a);
+        else if (chunks <= 16) fwd_pool<16, 1, true, TabT>(a);
+        else if (chunks <= 32) fwd_pool<32, 1, true, TabT>(a);
+        else if (chunks <= 64) fwd_pool<64, 1, true, TabT>(a);
+        else fwd_pool<64, 2, true, TabT>(a);
         a.num_bags = 0;  // what remains for the generic launcher is rows_out
     }
     fwd_dispatch<TabT>(a);
@@ -499,7 +511,7 @@ int np_lookup_fwd_t(const void* table, int32_t table_dtype, int64_t num_rows, in
     if (!np::aligned(table, row_align) || !np::aligned(out, out_dtype == NP_BF16 ? 8 : 16) || !np::aligned(rows_out, row_align))
         return NP_ERR_INVALID_ARG;
     if (mode == NP_SEQ && static_cast<int64_t>(num_bags) * max_len > INT32_MAX) return NP_ERR_UNSUPPORTED;
-    np::FwdArgs a{table, dim, list_keys, d_num_list, cap, idx, bag_offsets, num_bags, mode, max_len, out_dtype, out, rows_out,
+    np::FwdArgs a{table, dim, list_keys, d_num_list, cap, idx, bag_offsets, num_bags, n, mode, max_len, out_dtype, out, rows_out,
                   static_cast<hipStream_t>(stream)};
     if (table_dtype == NP_BF16) {
         np::fwd_16bit<uint16_t>(a, static_cast<const uint16_t*>(table));
