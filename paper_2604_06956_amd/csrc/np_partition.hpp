@@ -237,50 +237,43 @@ part_hist_kernel(P pol, int n_host, const int* __restrict__ d_n, int bins, Chunk
     for (int b = threadIdx.x; b < bins; b += kHistThreads) H[static_cast<size_t>(c) * bins + b] = lh[b];
 }
 
-// Block = 16 waves x 64 bins: wave y sums, then rewrites as exclusive prefixes, its slice of the chunks.
+// Block = 16 waves x 64 bins: wave y sums, then rewrites as exclusive prefixes, its slice of the chunks.  Bound by latency
+// (2-8 MB of histogram rows that the kernel before has just written): every thread holds its slice of a column in registers,
+// all loads in flight at once, and reads it once.
 template <int THREADS>
 __global__ void __launch_bounds__(THREADS)
 part_colscan_kernel(uint32_t* __restrict__ H, int num_chunks, int bins, uint32_t* __restrict__ bin_total) {
     constexpr int NY = THREADS / kWave;
+    constexpr int kSlice = kTargetChunks / NY;
+    static_assert(kTargetChunks % NY == 0, "a slice per wave");
     __shared__ uint32_t part[NY][kWave];
     const int lane = threadIdx.x % kWave, y = threadIdx.x / kWave;
     const int bin = blockIdx.x * kWave + lane;
-    const int per = (num_chunks + NY - 1) / NY;
+    const int per = (num_chunks + NY - 1) / NY;  // <= kSlice
     const int c0 = y * per;
-    const int c1 = c0 + per < num_chunks ? c0 + per : num_chunks;
+    const int cnt = bin < bins ? (c0 + per < num_chunks ? per : num_chunks - c0) : 0;
+    uint32_t t[kSlice];
     uint32_t sum = 0;
-    if (bin < bins) {
-        for (int c = c0; c < c1; c += 8) {
-            uint32_t t[8];
+    uint32_t* col = H + static_cast<size_t>(c0) * bins + bin;
 #pragma unroll
-            for (int q = 0; q < 8; ++q) t[q] = c + q < c1 ? H[static_cast<size_t>(c + q) * bins + bin] : 0u;
+    for (int q = 0; q < kSlice; ++q) t[q] = q < cnt ? col[static_cast<size_t>(q) * bins] : 0u;
 #pragma unroll
-            for (int q = 0; q < 8; ++q) sum += t[q];
-        }
-    }
+    for (int q = 0; q < kSlice; ++q) sum += t[q];
     part[y][lane] = sum;
     __syncthreads();
-    uint32_t base = 0, total = 0;
+    uint32_t run = 0, total = 0;
 #pragma unroll
     for (int yy = 0; yy < NY; ++yy) {
         const uint32_t s = part[yy][lane];
-        if (yy < y) base += s;
+        if (yy < y) run += s;
         total += s;
     }
-    if (bin < bins) {
-        uint32_t run = base;
-        for (int c = c0; c < c1; c += 8) {
-            uint32_t t[8];
 #pragma unroll
-            for (int q = 0; q < 8; ++q) t[q] = c + q < c1 ? H[static_cast<size_t>(c + q) * bins + bin] : 0u;
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                if (c + q < c1) H[static_cast<size_t>(c + q) * bins + bin] = run;
-                run += t[q];
-            }
-        }
-        if (y == 0) bin_total[bin] = total;
+    for (int q = 0; q < kSlice; ++q) {
+        if (q < cnt) col[static_cast<size_t>(q) * bins] = run;
+        run += t[q];
     }
+    if (y == 0 && bin < bins) bin_total[bin] = total;
 }
 
 // Stable rank of every item among the items of its wave with the same digit.  The wave's IPT * 64 items are the tile's items
