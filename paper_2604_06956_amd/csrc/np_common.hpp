@@ -214,13 +214,35 @@ __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_floa
 
 // A row "word" is four consecutive elements: 16 bytes of an fp32 row, 8 bytes of a bf16 row.  Reading a bf16 word
 // widens exactly; writing one rounds to nearest even.
-__device__ __forceinline__ float4 load_word(const float* row, int w) { return reinterpret_cast<const float4*>(row)[w]; }
+//
+// RawWord is a word as it lies in memory.  A kernel that keeps several rows in flight loads raw words and widens them where they
+// are used: a conversion right behind a load inside a condition makes the compiler wait for that load there, so that the rows
+// come in one after the other.
+template <typename T> struct RawWordOf { using type = uint2; };
+template <> struct RawWordOf<float> { using type = float4; };
+template <typename T> using RawWord = typename RawWordOf<T>::type;
 
-__device__ __forceinline__ float4 load_word(const uint16_t* row, int w) {
-    const uint2 u = reinterpret_cast<const uint2*>(row)[w];
+__device__ __forceinline__ float4 zero_raw(const float*) { return make_float4(0.f, 0.f, 0.f, 0.f); }
+__device__ __forceinline__ uint2 zero_raw(const void*) { return make_uint2(0u, 0u); }  // 16-bit zeros
+
+template <typename T>
+__device__ __forceinline__ RawWord<T> load_raw(const T* row, int w) { return reinterpret_cast<const RawWord<T>*>(row)[w]; }
+
+__device__ __forceinline__ float4 widen_word(const float*, const float4& u) { return u; }
+
+__device__ __forceinline__ float4 widen_word(const uint16_t*, const uint2& u) {
     return make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xFFFF0000u), __uint_as_float(u.y << 16),
                        __uint_as_float(u.y & 0xFFFF0000u));
 }
+
+// fp16 rows are typed __half (bf16 rows are uint16_t): same 8-byte words, hardware conversions (nearest even).
+__device__ __forceinline__ float4 widen_word(const __half*, const uint2& u) {
+    const __half2 lo = *reinterpret_cast<const __half2*>(&u.x), hi = *reinterpret_cast<const __half2*>(&u.y);
+    return make_float4(__low2float(lo), __high2float(lo), __low2float(hi), __high2float(hi));
+}
+
+template <typename T>
+__device__ __forceinline__ float4 load_word(const T* row, int w) { return widen_word(row, load_raw(row, w)); }
 
 __device__ __forceinline__ uint2 pack_bf16x4(const float4& a) {
     uint2 o;
@@ -235,13 +257,6 @@ __device__ __forceinline__ void store_word_stream(float* row, int w, const float
 
 __device__ __forceinline__ void store_word_stream(uint16_t* row, int w, const float4& a) {
     store_stream(reinterpret_cast<uint2*>(row) + w, pack_bf16x4(a));
-}
-
-// fp16 rows are typed __half (bf16 rows are uint16_t): same 8-byte words, hardware conversions (nearest even).
-__device__ __forceinline__ float4 load_word(const __half* row, int w) {
-    const uint2 u = reinterpret_cast<const uint2*>(row)[w];
-    const __half2 lo = *reinterpret_cast<const __half2*>(&u.x), hi = *reinterpret_cast<const __half2*>(&u.y);
-    return make_float4(__low2float(lo), __high2float(lo), __low2float(hi), __high2float(hi));
 }
 
 // fp32 -> fp16, nearest even, of a value that has already been rounded to fp32.  The empty asm pins the fp32 value in

@@ -295,31 +295,49 @@ __device__ __forceinline__ int group_bcast(int v, int src_in_group) {
     return __shfl(v, (__lane_id() & ~(LPR - 1)) + src_in_group, kWave);
 }
 
-// Row `row` (non-negative, below 2^31) of dY: one 32x32->64 multiply for the byte offset.
-__device__ __forceinline__ float4 load_dy(const float* dY, int row, int dim, int word) {
-    const uint64_t off = static_cast<uint64_t>(static_cast<uint32_t>(row)) * static_cast<uint32_t>(dim * 4);
-    return reinterpret_cast<const float4*>(reinterpret_cast<const char*>(dY) + off)[word];
+// Word `word` of row `row` (non-negative, below 2^31) of dY, as it lies in memory: one 32x32->64 multiply for the byte offset.
+template <typename T>
+__device__ __forceinline__ const T* dy_row(const T* dY, int row, int dim) {
+    const uint64_t off = static_cast<uint64_t>(static_cast<uint32_t>(row)) * static_cast<uint32_t>(dim * static_cast<int>(sizeof(T)));
+    return reinterpret_cast<const T*>(reinterpret_cast<const char*>(dY) + off);
 }
 
-__device__ __forceinline__ float4 load_dy(const uint16_t* dY, int row, int dim, int word) {
-    const uint64_t off = static_cast<uint64_t>(static_cast<uint32_t>(row)) * static_cast<uint32_t>(dim * 2);
-    const uint2 p = reinterpret_cast<const uint2*>(reinterpret_cast<const char*>(dY) + off)[word];
-    return make_float4(__uint_as_float(p.x << 16), __uint_as_float(p.x & 0xFFFF0000u), __uint_as_float(p.y << 16),
-                       __uint_as_float(p.y & 0xFFFF0000u));
-}
+// What a lane of bwd_main holds of a dY row in flight: NV raw words, or, in a PAIR kernel, the bf16 words 2r and 2r + 1 with
+// one 16-byte load (rows a multiple of 8 elements wide, 16-byte aligned base; twice the bytes per load instruction).  16-bit
+// words are widened in the walk, behind its one wait: widened in the load's own condition they waited for every row in turn.
+// Whole passes, before and after, the 16-bit table rows of the fused step and of the pooling kernels among it: sequence batch
+// 2606 -> 2464 us (9.8 M lookups, bf16 rows of 128), fused call on a bf16 table 1348 -> 1199 (10.5 M lookups, dim 64), bf16
+// activations on wide ids 488 -> 469, 7000 fp16 bags of 36 wide rows 118 -> 107.
+template <typename T, int NV, bool PAIR>
+struct RowInFlight {
+    RawWord<T> w[NV];
+    __device__ __forceinline__ void clear() {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) w[v] = zero_raw(static_cast<const T*>(nullptr));
+    }
+    template <int LPR>
+    __device__ __forceinline__ void load(const T* dY, int row, int dim, int r, int words) {
+        const T* src = dy_row(dY, row, dim);
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+            if (r + v * LPR < words) w[v] = load_raw(src, r + v * LPR);
+    }
+    __device__ __forceinline__ float4 word(int v) const { return widen_word(static_cast<const T*>(nullptr), w[v]); }
+};
 
-// Words 2 * pair and 2 * pair + 1 of a bf16 row with one 16-byte load (rows a multiple of 8 elements wide, 16-byte
-// aligned base).  Twice the bytes per load instruction: with 8-byte lanes the gather of 256-byte bf16 rows in
-// sequence mode ran at half the rate of the fp32 one.
-__device__ __forceinline__ void load_dy_pair(const uint16_t* dY, int row, int dim, int pair, float4& a, float4& b) {
-    const uint64_t off = static_cast<uint64_t>(static_cast<uint32_t>(row)) * static_cast<uint32_t>(dim * 2);
-    const uint4 p = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(dY) + off)[pair];
-    a = make_float4(__uint_as_float(p.x << 16), __uint_as_float(p.x & 0xFFFF0000u), __uint_as_float(p.y << 16),
-                    __uint_as_float(p.y & 0xFFFF0000u));
-    b = make_float4(__uint_as_float(p.z << 16), __uint_as_float(p.z & 0xFFFF0000u), __uint_as_float(p.w << 16),
-                    __uint_as_float(p.w & 0xFFFF0000u));
-}
-__device__ __forceinline__ void load_dy_pair(const float*, int, int, int, float4&, float4&) {}  // never selected
+template <int NV>
+struct RowInFlight<uint16_t, NV, true> {
+    static_assert(NV == 2, "a pair of words per lane");
+    uint4 w;
+    __device__ __forceinline__ void clear() { w = make_uint4(0u, 0u, 0u, 0u); }
+    template <int LPR>
+    __device__ __forceinline__ void load(const uint16_t* dY, int row, int dim, int r, int words) {
+        if (2 * r < words) w = reinterpret_cast<const uint4*>(dy_row(dY, row, dim))[r];  // words is even here
+    }
+    __device__ __forceinline__ float4 word(int v) const {
+        return widen_word(static_cast<const uint16_t*>(nullptr), v == 0 ? make_uint2(w.x, w.y) : make_uint2(w.z, w.w));
+    }
+};
 
 // Variant (tunable "bwd_singles_by_bag", pooled modes, fp32 upstream gradients, plain sink): a key with ONE lookup needs no
 // reduction, its gradient row is a copy of its bag's upstream row.  Such keys are served bag by bag, each upstream row
@@ -370,7 +388,7 @@ bwd_single_copy_kernel(const float* __restrict__ dY, int dim, const int32_t* __r
             for (int v = 0; v < NV; ++v) {
                 const int wv = r + v * LPR;
                 float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (wv < words) t = load_dy(dY, static_cast<int>(b), dim, wv);
+                if (wv < words) t = load_word(dy_row(dY, static_cast<int>(b), dim), wv);
                 // the first (and only) step of the key-major running sum
                 if (MEAN) x[v] = make_float4(fmaf(w, t.x, 0.f), fmaf(w, t.y, 0.f), fmaf(w, t.z, 0.f), fmaf(w, t.w, 0.f));
                 else x[v] = make_float4(0.f + t.x, 0.f + t.y, 0.f + t.z, 0.f + t.w);
@@ -523,23 +541,14 @@ bwd_main_kernel(const DyT* __restrict__ dY, int dim, int seq, int max_len, const
     const int rel_raw = occ_offsets[cand <= U ? cand : U] - tile_start;
     const int seg0_start = occ_offsets[u0];
     const int j = (valid && !indexed) ? load_stream(occ + i) : 0;
-    float4 x[kBwdUnroll][NV];
+    RowInFlight<DyT, NV, PAIR> x[kBwdUnroll];
     // rows of positions k0 .. k0 + kBwdUnroll - 1 of the strip; a position without a row (sr < 0) or past `limit` loads nothing
     auto load_batch = [&](int k0, int limit) {
 #pragma unroll
         for (int q = 0; q < kBwdUnroll; ++q) {
             const int srk = group_bcast<LPR>(sr, (k0 + q) & (LPR - 1));
-            const bool on = k0 + q < limit && srk >= 0;
-            if constexpr (PAIR) {
-                x[q][0] = x[q][1] = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (on && 2 * r < words) load_dy_pair(dY, srk, dim, r, x[q][0], x[q][1]);  // words is even here
-            } else {
-#pragma unroll
-                for (int v = 0; v < NV; ++v) {
-                    const int wv = r + v * LPR;
-                    x[q][v] = (on && wv < words) ? load_dy(dY, srk, dim, wv) : make_float4(0.f, 0.f, 0.f, 0.f);
-                }
-            }
+            x[q].clear();
+            if (k0 + q < limit && srk >= 0) x[q].template load<LPR>(dY, srk, dim, r, words);
         }
     };
     const bool early = indexed && !skip_singles;  // (the single-lookup variant decides later which rows it does not want)
@@ -624,8 +633,8 @@ bwd_main_kernel(const DyT* __restrict__ dY, int dim, int seq, int max_len, const
     float4 acc[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) acc[v] = make_float4(0.f, 0.f, 0.f, 0.f);
-    float4 tw[kSinkAhead ? kBwdUnroll : 1][NV];
     using TabT = typename SinkTable<FUSED>::type;
+    RawWord<TabT> tw[kSinkAhead ? kBwdUnroll : 1];
     // table rows of the tails among positions k0 .. k0 + kBwdUnroll - 1 that are finished inside this walk
     auto load_table_batch = [&](int k0) {
         if constexpr (kSinkAhead) {
@@ -637,7 +646,7 @@ bwd_main_kernel(const DyT* __restrict__ dY, int dim, int seq, int max_len, const
                                                          static_cast<uint32_t>(group_bcast<LPR>(skey_lo, kk)));
                 const bool need = k0 + q < cnt && dkq >= 0 && !(first_cut && k0 + q == first_tail) && r < words;
                 const TabT* wrow = static_cast<const TabT*>(sink.table) + static_cast<size_t>(key) * dim;
-                tw[q][0] = need ? load_word(wrow, r) : make_float4(0.f, 0.f, 0.f, 0.f);
+                tw[q] = need ? load_raw(wrow, r) : zero_raw(wrow);
             }
         }
     };
@@ -656,16 +665,17 @@ bwd_main_kernel(const DyT* __restrict__ dY, int dim, int seq, int max_len, const
                 const float wk = MEAN ? __int_as_float(group_bcast<LPR>(wbits, k)) : 1.f;
 #pragma unroll
                 for (int v = 0; v < NV; ++v) {
+                    const float4 xv = x[q].word(v);
                     if (MEAN) {
-                        acc[v].x = fmaf(wk, x[q][v].x, acc[v].x);
-                        acc[v].y = fmaf(wk, x[q][v].y, acc[v].y);
-                        acc[v].z = fmaf(wk, x[q][v].z, acc[v].z);
-                        acc[v].w = fmaf(wk, x[q][v].w, acc[v].w);
+                        acc[v].x = fmaf(wk, xv.x, acc[v].x);
+                        acc[v].y = fmaf(wk, xv.y, acc[v].y);
+                        acc[v].z = fmaf(wk, xv.z, acc[v].z);
+                        acc[v].w = fmaf(wk, xv.w, acc[v].w);
                     } else {
-                        acc[v].x += x[q][v].x;
-                        acc[v].y += x[q][v].y;
-                        acc[v].z += x[q][v].z;
-                        acc[v].w += x[q][v].w;
+                        acc[v].x += xv.x;
+                        acc[v].y += xv.y;
+                        acc[v].z += xv.z;
+                        acc[v].w += xv.w;
                     }
                 }
                 if (dk >= 0) {  // a segment ends here
@@ -680,7 +690,9 @@ bwd_main_kernel(const DyT* __restrict__ dY, int dim, int seq, int max_len, const
                             const int64_t key = static_cast<int64_t>((static_cast<uint64_t>(static_cast<uint32_t>(group_bcast<LPR>(skey_hi, k))) << 32) |
                                                                      static_cast<uint32_t>(group_bcast<LPR>(skey_lo, k)));
                             const float so = __int_as_float(group_bcast<LPR>(__float_as_int(sold), k));
-                            sink_row_loaded<LPR, NV, FUSED>(sink, key, so, dim, r, words, tw[q], acc);
+                            float4 trow[NV];  // NV is 1 here
+                            trow[0] = widen_word(static_cast<const TabT*>(nullptr), tw[q]);
+                            sink_row_loaded<LPR, NV, FUSED>(sink, key, so, dim, r, words, trow, acc);
                         } else {
                             sink_row<LPR, NV, FUSED>(sink, dk, dim, r, words, acc);
                         }

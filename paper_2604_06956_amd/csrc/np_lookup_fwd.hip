@@ -67,7 +67,7 @@ fwd_pool_kernel(const TabT* __restrict__ table, int dim, const int64_t* __restri
         const int off_lo = static_cast<int>(row_off & 0xFFFFFFFFll), off_hi = static_cast<int>(row_off >> 32);
         const int cnt = hi - base < LPR ? hi - base : LPR;
         for (int k0 = 0; k0 < cnt; k0 += UN) {
-            float4 x[UN][NV];
+            RawWord<TabT> x[UN][NV];
 #pragma unroll
             for (int q = 0; q < UN; ++q) {
                 const bool on = k0 + q < cnt;  // uniform inside the group; k0 + q < LPR always
@@ -78,17 +78,18 @@ fwd_pool_kernel(const TabT* __restrict__ table, int dim, const int64_t* __restri
 #pragma unroll
                 for (int v = 0; v < NV; ++v) {
                     const int wv = r + v * LPR;
-                    x[q][v] = (on && wv < words) ? load_word(src, wv) : make_float4(0.f, 0.f, 0.f, 0.f);
+                    x[q][v] = (on && wv < words) ? load_raw(src, wv) : zero_raw(src);
                 }
             }
 #pragma unroll
             for (int q = 0; q < UN; ++q) {
 #pragma unroll
                 for (int v = 0; v < NV; ++v) {  // rows that were not loaded are zeros
-                    acc[v].x += x[q][v].x;
-                    acc[v].y += x[q][v].y;
-                    acc[v].z += x[q][v].z;
-                    acc[v].w += x[q][v].w;
+                    const float4 a = widen_word(table, x[q][v]);
+                    acc[v].x += a.x;
+                    acc[v].y += a.y;
+                    acc[v].z += a.z;
+                    acc[v].w += a.w;
                 }
             }
         }
@@ -303,14 +304,14 @@ fwd_seq_kernel(const TabT* __restrict__ table, int dim, const int64_t* __restric
     const int words = dim / 4;
     int64_t off[SPG];
     seq_row_offsets<LPR, SPG, static_cast<int>(sizeof(TabT))>(wq0, total, max_len, dim, list_keys, idx, bag_offsets, off);
-    float4 x[SPG][NV];
+    RawWord<TabT> x[SPG][NV];
 #pragma unroll
     for (int k = 0; k < SPG; ++k) {
         const TabT* src = reinterpret_cast<const TabT*>(reinterpret_cast<const char*>(table) + (off[k] < 0 ? 0 : off[k]));
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
             const int wv = r + v * LPR;
-            x[k][v] = (off[k] >= 0 && wv < words) ? load_word(src, wv) : make_float4(0.f, 0.f, 0.f, 0.f);
+            x[k][v] = (off[k] >= 0 && wv < words) ? load_raw(src, wv) : zero_raw(src);
         }
     }
 #pragma unroll
@@ -320,7 +321,7 @@ fwd_seq_kernel(const TabT* __restrict__ table, int dim, const int64_t* __restric
 #pragma unroll
             for (int v = 0; v < NV; ++v) {
                 const int wv = r + v * LPR;
-                if (wv < words) store_words(out + static_cast<size_t>(q) * dim + wv * 4, x[k][v]);
+                if (wv < words) store_words(out + static_cast<size_t>(q) * dim + wv * 4, widen_word(table, x[k][v]));
             }
         }
     }
