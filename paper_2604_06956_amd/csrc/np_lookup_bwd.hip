@@ -118,11 +118,12 @@ __device__ __forceinline__ void bagmap_block(int blk, const int32_t* __restrict_
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int64_t b = chunk + q * 256 + t;
-            o[q] = bag_offsets[b < num_bags ? b : num_bags];  // bag_offsets[num_bags] = n: never below `end`
+            o[q] = bag_offsets[b < num_bags ? b : num_bags - 1];
+            if (b >= num_bags) o[q] = end;  // no bag: starts nothing here
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            if (o[q] < end) {
+            if (o[q] >= base && o[q] < end) {  // (offsets ascend: >= base always; keeps broken ones out of the arrays' neighbours)
                 const int wd = (o[q] - base) >> 6, k = (o[q] - base) & 63;
                 if (k == 0) {
                     atomicAdd(&on_first[wd], 1);
@@ -139,7 +140,8 @@ __device__ __forceinline__ void bagmap_block(int blk, const int32_t* __restrict_
     int total;
     const int before = block_excl_scan<256 / kWave>(mine, scan_tmp, &total);
     if (t < WORDS && base + t * 64 < end) {
-        const int bag = b0 + before + on_first[t] - 1;  // last bag that starts at or before the block's first lookup
+        // last bag that starts at or before the block's first lookup; held inside the batch whatever the offsets say
+        const int bag = max(0, min(b0 + before + on_first[t], num_bags) - 1);
         BagMapEntry e;
         e.starts = starts[t];
         e.bag0 = again[t] ? (bag | static_cast<int32_t>(0x80000000u)) : bag;
