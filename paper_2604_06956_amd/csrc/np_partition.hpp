@@ -548,20 +548,24 @@ part_scatter_kernel(P pol, int n_host, const int* __restrict__ d_n, int bins, in
 // chain of loads, not by bytes, so it takes fewer of both:
 //   up to kSoloItems               ONE kernel.  Every block counts the digits of the whole input itself, those before its own
 //                                  tile apart, ranks its tile and writes it out.  It grows by 0.3 us per thousand items
-//   items x bins <= kSmallProduct  part_hist over at most kSmallChunks chunks, then the same kernel, which reads the histogram
-//                                  rows itself instead of having the columns scanned by a launch of their own
+//   items x bins <= kSmallProduct  part_hist, then the same kernel, which reads the histogram rows itself instead of having the
+//                                  columns scanned by a launch of their own.  Every chunk is one tile there: at most
+//                                  kTargetChunks of them, and at most 2^15 words of histogram for a block to read
 // Items go straight to their places (no reordering through LDS): L2 holds the whole output.
 // np_dedup (sort and ranking), us, three launches a pass -> this: 17-bit keys (512 bins) 2 k 34 -> 18, 16 k 40 -> 30,
 // 64 k 41 -> 36, 256 k 45 -> 41, 512 k 49 -> 54; 20 bits (1024 bins) 128 k 45 -> 42, 256 k 47 -> 49; 22 bits (2048 bins)
 // 64 k 48 -> 44, 128 k 50 -> 50; one kernel against two: 16 k 30 / 35, 32 k 41 / 36, 64 k 60 / 36.
+// np_route, three launches -> two, all of the bound / a tenth of it in use: 1 or 8 shards, bound 1 M 22 -> 18 / 20 -> 16,
+// 2 M 35 -> 30 / 25 -> 19; 64 shards, 1 M 22 -> 23 / 20 -> 17, 2 M 36 -> 41 / 26 -> 22.  Chunks of several tiles lose: the
+// direct stores on 64 chunks took 366 us for 16 M keys and one shard, 154 with three launches.
 constexpr int kSmallThreads = 1024;
 constexpr int kSmallWaves = kSmallThreads / kWave;
 constexpr int kSmallMaxBins = 2048;  // 16 two-byte counters per bin: 64 KB of LDS
-constexpr int kSmallChunks = 64;
 constexpr int kSoloIPT = 2;
 constexpr int kSoloTile = kSmallThreads * kSoloIPT;
 constexpr int kSoloItems = 24 * 1024;
-constexpr int64_t kSmallProduct = int64_t(1) << 27;
+constexpr int64_t kSmallProduct = int64_t(1) << 27;  // 2^15 histogram words x kPartTile items
+constexpr int64_t kSmallItems = static_cast<int64_t>(kTargetChunks) * kPartTile;
 
 inline size_t part_small_lds_bytes(int bins) {
     const size_t words = (sizeof(uint32_t) * 2 * static_cast<size_t>(bins) + 64 + 15) / 16 * 16;
@@ -704,7 +708,8 @@ template <class P>
 inline void run_partition_pass(const P& pol, int n_host, const int* d_n, int bins, int nbits, const ChunkPlan& plan,
                                uint32_t* H, uint32_t* bin_total, int32_t* totals_out, int32_t* offsets_out,
                                hipStream_t stream, const char* tag_hist, const char* tag_scan, const char* tag_scatter) {
-    if (bins <= kSmallMaxBins && (n_host <= kSoloItems || static_cast<int64_t>(n_host) * bins <= kSmallProduct)) {
+    if (bins <= kSmallMaxBins &&
+        (n_host <= kSoloItems || (n_host <= kSmallItems && static_cast<int64_t>(n_host) * bins <= kSmallProduct))) {
         static std::atomic<int> granted_small[2][kMaxDevices];
         const size_t lds = part_small_lds_bytes(bins);
         if (n_host <= kSoloItems) {
@@ -715,13 +720,11 @@ inline void run_partition_pass(const P& pol, int n_host, const int* d_n, int bin
             return;
         }
         constexpr int kIPT = kPartTile / kSmallThreads;
-        ChunkPlan few = plan;
-        if (few.num_chunks > kSmallChunks) few.num_chunks = kSmallChunks;
         allow_dynamic_lds(reinterpret_cast<const void*>(part_small_kernel<P, kIPT, false>), lds, granted_small[1]);
-        NP_LAUNCH(tag_hist, part_hist_kernel<P>, dim3(few.num_chunks), dim3(kHistThreads), sizeof(uint32_t) * bins, stream, pol, n_host,
-                  d_n, bins, few, H);
-        NP_LAUNCH(tag_scatter, (part_small_kernel<P, kIPT, false>), dim3(few.num_chunks), dim3(kSmallThreads), lds, stream, pol, n_host, d_n,
-                  bins, nbits, few, H, totals_out, offsets_out);
+        NP_LAUNCH(tag_hist, part_hist_kernel<P>, dim3(plan.num_chunks), dim3(kHistThreads), sizeof(uint32_t) * bins, stream, pol, n_host,
+                  d_n, bins, plan, H);
+        NP_LAUNCH(tag_scatter, (part_small_kernel<P, kIPT, false>), dim3(plan.num_chunks), dim3(kSmallThreads), lds, stream, pol, n_host, d_n,
+                  bins, nbits, plan, H, totals_out, offsets_out);
         return;
     }
     NP_LAUNCH(tag_hist, part_hist_kernel<P>, dim3(plan.num_chunks), dim3(kHistThreads), sizeof(uint32_t) * bins, stream,

@@ -40,9 +40,12 @@ def test_dedup_at_the_edges_of_its_forms(H, bits, skew):
         H.assert_dedup_equal(g, keys)
 
 
-@pytest.mark.parametrize("S", [1, 37, 1536, 2048, 2049])
-@pytest.mark.parametrize("cap", [1, 2048, 24576, 24577, 65536, 65537, 300000])
-def test_route_at_the_edges_of_its_forms(H, cap, S):
+CAPS = [1, 2048, 24576, 24577, 65536, 65537, 300000]
+
+
+@pytest.mark.parametrize("S,cap", [(S, cap) for S in (1, 37, 1536, 2048, 2049) for cap in CAPS] +
+                         [(S, cap) for S in (1, 64, 65) for cap in (1 << 21, (1 << 21) + 1)])  # the largest two-launch form, and past it
+def test_route_at_the_edges_of_its_forms(H, S, cap):
     rng = np.random.default_rng(cap + S)
     for U in sorted({0, 1, cap // 3, cap}):      # the bound is the batch size, the count a part of it
         H.progress(f"np_route cap={cap} S={S} U={U}")
